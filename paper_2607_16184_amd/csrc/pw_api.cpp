@@ -116,9 +116,12 @@ struct WsLayout {
 
 // Which GEMM kernels serve a range, from its expected slots per expert
 // S / ne: up to 48, the decode kernels (weights streamed in registers, exact
-// code-domain arithmetic, up to four 16-slot tiles per pass); up to 127, the
-// streaming kernel with 64-slot tiles; from 128, the LDS-tiled 256 x 256
-// kernel. The shared experts of a decode-sized batch are a few experts with a
+// code-domain arithmetic, up to four 16-slot tiles per pass); above, the
+// LDS-tiled kernel (256 weight rows x 128 or 256 slots; at 55, 75 and 105
+// slots per expert of 4096 x 14336 it takes 441, 490 and 500 us a step, the
+// streaming kernel 493, 641 and 664 us). The streaming kernel (64-slot tiles)
+// serves bit-plane layers and shapes whose down projection is not a multiple
+// of 256 rows. The shared experts of a decode-sized batch are a few experts with a
 // few hundred slots each: where the tiled kernel's tiles would not give every
 // CU a workgroup, the streaming kernel's smaller tiles spread their work. The
 // last two need 32/64-row staging inside one page, 128-row down blocks and
@@ -131,7 +134,7 @@ GemmPath pick_path(const pw_layer_desc& d, size_t S, size_t S_all, int ne, bool 
   const bool tiles = fits && d.G >= 64 && d.R % 64 == 0 && d.F % 128 == 0;
   // nested bit-plane pages are read by the streaming kernel only
   if (apl) return GemmPath::kStream;
-  if (expect >= 128 && tiles && d.H % 256 == 0) {
+  if (expect > 48 && tiles && d.H % 256 == 0) {
     const size_t tiled_wgs = static_cast<size_t>(ne) * ((expect + 255) / 256) * (d.F / 128);
     return shared && tiled_wgs < kCUs ? GemmPath::kStream : GemmPath::kTiled;
   }

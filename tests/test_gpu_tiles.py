@@ -1,0 +1,51 @@
+"""Edges of the tiled paged GEMM: expert slot counts around the tile widths,
+every group layout (scale/zero groups of 64, 128, 256 values in 4- and 8-bit
+units), short reductions and mixed page formats, against the CPU oracle.
+
+The kernel multiplies quantized weights rounded to the activation dtype
+(w_round) and rounds the SwiGLU output there too; what is left between the
+two is the order of fp32 sums over K <= 640 products, far below the 1e-3
+allowed (the bound the other fp32 parity tests use).
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+from helpers import gpu_layer, oracle_layer, rel_err, say, to_dev, to_dev16
+from paper_2607_16184_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+F16, BF16 = synth.F16, synth.BF16
+
+
+@pytest.mark.parametrize("counts,H,F,R,G,act,sdt", [
+    ((1, 127, 128, 129), 256, 256, 64, 64, F16, F16),       # 128-slot tiles, one slot, full, one over
+    ((63, 0, 250, 65), 256, 384, 64, 128, BF16, BF16),      # an empty expert, two tiles
+    ((255, 256, 257, 0), 512, 256, 128, 256, BF16, F16),    # 256-slot tiles
+    ((500, 16, 17, 15), 256, 640, 64, 64, BF16, BF16),      # skew: idle waves in most tiles
+    ((300, 129, 240, 1), 768, 128, 128, 128, F16, BF16),    # K = 128: one block per row of the down pages
+    ((100, 90, 70, 120), 384, 256, 64, 64, BF16, BF16),     # H not a multiple of 256: the streaming kernel
+])
+def test_tile_edges(counts, H, F, R, G, act, sdt):
+    import torch
+    E, T = len(counts), sum(counts)
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], E=E, K=1, H=H, F=F, R=R, G=min(G, H, F), T=T, act=act, sdt=sdt)
+    w16 = [synth.expert_weights(cfg, p) for p in range(3)]
+    bits = synth.bitmap(cfg)
+    say("tiles %s H=%d F=%d G=%d act=%d" % (counts, H, F, cfg.G, act))
+    L = gpu_layer(cfg, w16, bits, synth.pool_order(cfg))
+    O = oracle_layer(cfg, w16, bits)
+    lg = synth.logits(cfg).copy()
+    own = np.random.default_rng(3).permutation(np.repeat(np.arange(E), counts))
+    lg[np.arange(T), own] += 100.0
+    x16 = synth.activations(cfg)
+    y = L.forward(to_dev16(x16), L.route(to_dev(lg), 1), out_fp32=True)
+    torch.cuda.synchronize()
+    ids, w = oracle.route(lg, 1)
+    assert np.array_equal(np.bincount(ids[:, 0], minlength=E), counts)
+    e = rel_err(y.cpu().numpy(), O.forward(x16, ids, w, h_round=True, w_round=True))
+    assert e <= 1e-3, e
+    L.close()
