@@ -174,11 +174,13 @@ pw_status pw_route_topk(const float* logits, int T, int E, int K, int renorm,
  * token's last n_shared columns must be the shared experts (in order), its
  * first columns routed experts only. The GEMM runs the routed and the shared
  * experts as separate launches, each with the kernels suited to its slots
- * per expert (a shared expert has T); the shared experts' launches go to a
- * stream of the layer's own, forked from the caller's stream and joined back
- * before the combine, so that they run beside the routed ones (under graph
- * capture: two branches; with pw_layer_set_chains(layer, 1), on the
- * caller's stream after them). That stream (default priority) and its two
+ * per expert (a shared expert has T). In layers of 256 MiB of pages or more
+ * the shared experts' launches go to a stream of the layer's own, forked
+ * from the caller's stream and joined back before the combine, so that they
+ * run beside the routed ones (under graph capture: two branches); in smaller
+ * layers, where the fork costs more than it hides, and with
+ * pw_layer_set_chains(layer, 1), they follow them on the caller's stream.
+ * That stream (default priority) and its two
  * events live on the pool's device (created with the layer by
  * pw_layer_create; pw_layer_destroy releases them). No GPU work; takes
  * effect for the next GEMM call.                                           */
@@ -187,14 +189,18 @@ pw_status pw_layer_set_shared_experts(pw_layer* layer, int n_shared);
 /* Concurrent expert chains (Sec. 3.3 runs the MoE forward as one fused
  * kernel; here its gate/up and down phases are separate launches, and this
  * setting overlaps the boundary between them). With
- * chains = 2 (the default), when a call's experts run on the decode kernels
- * and the layer has no shared experts, they are split into two halves, each
+ * chains = 2 (the default), when a call is captured into a graph, its experts
+ * run on the decode kernels with a slot or more expected for each, the layer
+ * holds 256 MiB of pages or more and has no shared experts, they are split
+ * into two halves, each
  * a chain of gate/up then down: the first on the caller's stream, the
  * second on the layer's own stream (forked from the caller's and joined
- * back before the combine; under graph capture, two branches), so that the
+ * back before the combine: two branches of the graph), so that the
  * phase boundary of one chain overlaps the other's GEMMs; a layer with
  * shared experts runs those on the layer's stream instead (see
- * pw_layer_set_shared_experts). chains = 1 launches everything on the
+ * pw_layer_set_shared_experts). Calls that are not captured keep to the
+ * caller's stream: the fork and join cost them what the overlap gains.
+ * chains = 1 launches everything on the
  * caller's stream, one launch after another (each kernel alone on the GPU,
  * as a per-kernel timing needs). Results are identical either way (each
  * expert's rows are computed by the same kernels). PW_EINVAL unless chains

@@ -208,6 +208,31 @@ WsLayout ws_layout(const pw_layer_desc& d, int T, int K, bool apl, int n_shared)
   return w;
 }
 
+// Whether a call forks work to the layer's own stream. A fork and join cost a
+// few microseconds in a graph and 10 to 40 issued call by call (two more
+// launches, two event records and two cross-stream waits), so:
+//   small layers (pages below kForkPages) never fork;
+//   shared experts fork above that: their few workgroups run beside the
+//     routed ones (60 + 4 experts of 2048 x 1408, 128 tokens: 164 us a step
+//     against 179 call by call, 157 against 184 in a graph; at 16 tokens 110
+//     either way and 104 against 114);
+//   the second routed chain forks only under stream capture, and where every
+//     expert expects a slot: in a graph it gains (8 experts of 4096 x 14336,
+//     64 tokens: 340 us against 351; 2048 x 7168: 111 against 114; tiny layer
+//     39 against 21), call by call it gains nothing (345 against 346) or loses
+//     (33 tokens on 4- and 8-bit pages 189 against 186, one token 112 against
+//     100, tiny layer 64 against 21).
+constexpr uint64_t kForkPages = uint64_t(256) << 20;
+
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return status == hipStreamCaptureStatusActive;
+}
+
 // Waits until the work already enqueued on `st` has finished, so that slots
 // its kernels or copies write can be released after a later step of the same
 // call failed (a failing call must not hand out memory still being written).
@@ -678,9 +703,10 @@ pw_status pw_moe_paged_gemm(const pw_layer* Lc, const void* x, int T, int K, con
   // Launch units: with shared experts, the shared range runs on the layer's
   // own stream beside the routed one (its few workgroups share the chip with
   // the routed ones instead of running alone after them); without, a
-  // decode-sized routed range runs as two chains of gate/up then down over
-  // the two halves of its experts, the second on the layer's stream, so that
-  // the boundary between one chain's phases overlaps the other's GEMMs. The
+  // decode-sized routed range captured into a graph runs as two chains of
+  // gate/up then down over the two halves of its experts, the second on the
+  // layer's stream, so that the boundary between one chain's phases overlaps
+  // the other's GEMMs (see kForkPages for when either pays). The
   // layer's stream is forked from `stream` and joined back before the
   // combine. Units write disjoint rows of h and of the partials.
   struct Unit {
@@ -689,9 +715,10 @@ pw_status pw_moe_paged_gemm(const pw_layer* Lc, const void* x, int T, int K, con
   };
   Unit units[2];
   int nu = 0;
-  const bool shared_fork = L->chains == 2 && L->side && wl.r[0].ne > 0 && wl.r[1].ne > 0;
-  const bool split_routed =
-      L->chains == 2 && L->side && wl.r[1].ne <= 0 && wl.r[0].path == GemmPath::kDecode && wl.r[0].ne >= 2;
+  const bool may_fork = L->chains == 2 && L->side && L->st.alloc.used() >= kForkPages;
+  const bool shared_fork = may_fork && wl.r[0].ne > 0 && wl.r[1].ne > 0;
+  const bool split_routed = may_fork && wl.r[1].ne <= 0 && wl.r[0].path == GemmPath::kDecode && wl.r[0].ne >= 2 &&
+                            wl.r[0].S >= static_cast<size_t>(wl.r[0].ne) && capturing(st);
   if (split_routed) {
     units[0] = Unit{wl.r[0], st};
     units[0].r.ne = wl.r[0].ne / 2;

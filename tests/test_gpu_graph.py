@@ -3,6 +3,7 @@ replayed: every replay is bit-identical to the eager step, for each GEMM path
 (decode kernels, streaming kernel, LDS-tiled kernel), with eager work on the
 same stream between replays. Nothing in the step allocates or clears memory
 with a memset, so the captured launches are the eager ones."""
+import numpy as np
 import pytest
 
 from helpers import case, gpu_layer, say, to_dev, to_dev16
@@ -140,4 +141,51 @@ def test_chains_bit_identical_shared(T, kw):
         out[chains] = (L.forward(x, routing).clone(), L.forward(x, routing, out_fp32=True).clone())
     torch.cuda.synchronize()
     assert torch.equal(out[1][0], out[2][0]) and torch.equal(out[1][1], out[2][1])
+    L.close()
+
+
+@pytest.mark.parametrize("n_shared", [0, 2])
+def test_forked_layer_stream_bit_identical(n_shared):
+    """A layer large enough (256 MiB of pages) for its calls to fork: the
+    second expert chain under capture, the shared experts in every call. The
+    graph's replays and the eager calls give the bits of one chain."""
+    import torch
+    from paper_2607_16184_amd.layer import PagedLayer
+    E, T = 8 + n_shared, 40
+    cfg, w16, _, order = case("tiny_shared", E=E, H=2048, F=2816, T=T, n_shared=n_shared)
+    bits = [np.full((E, cfg.nrb(p)), 16, np.int32) for p in range(3)]
+    say("forked layer stream, n_shared=%d" % n_shared)
+    L = gpu_layer(cfg, w16, bits, order)
+    assert L.stats()[0] >= 256 << 20
+    L.set_shared_experts(n_shared)
+    logits, x = to_dev(synth.logits(cfg)), to_dev16(synth.activations(cfg))
+    gate = to_dev(synth.shared_gate(cfg)) if n_shared else None
+    rbuf = PagedLayer.routing_buffers(T, E, cfg.K + n_shared)
+    y = torch.empty((T, cfg.H), dtype=torch.float32, device="cuda")
+
+    def step(out):
+        L.forward(x, L.route_shared(logits, cfg.K, n_shared, gate=gate, out=rbuf), out_fp32=True, y=out)
+
+    L.set_chains(1)
+    step(y)
+    torch.cuda.synchronize()
+    want = y.clone()
+    L.set_chains(2)
+    step(y)
+    torch.cuda.synchronize()
+    assert torch.equal(y, want)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        step(y)
+    other = torch.empty_like(y)
+    for r in range(3):
+        y.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want), r
+        step(other)                                        # eager work in between
+        torch.cuda.synchronize()
+        assert torch.equal(other, want), r
     L.close()
