@@ -243,33 +243,6 @@ pw_status check_hip_last(const char* what) {
   return e == hipSuccess ? PW_OK : hip_fail(e, what);
 }
 
-// Load-time quantization (or 16-bit layout) of pages from 16-bit values, each
-// job with its own K, up to kMaxQJobs per launch (profiled with the requant
-// phase).
-pw_status run_qjobs(pw_layer* L, const std::vector<pw::QJob>& jobs, hipStream_t st) {
-  const pw_layer_desc& d = L->st.desc;
-  const int span = d.G > 128 ? d.G / 128 : 1;
-  for (size_t base = 0; base < jobs.size(); base += pw::kMaxQJobs) {
-    pw::QJobBatch b{};
-    b.n_jobs = static_cast<int>(std::min<size_t>(pw::kMaxQJobs, jobs.size() - base));
-    b.R = d.R;
-    b.G = d.G;
-    b.act = d.act;
-    b.sdt = d.sdt;
-    uint32_t items = 0;
-    for (int j = 0; j < b.n_jobs; ++j) {
-      b.job[j] = jobs[base + j];
-      b.job[j].item_base = items;
-      items += static_cast<uint32_t>(d.R / 16) * static_cast<uint32_t>((b.job[j].K / 128) / span);
-    }
-    b.total_items = items;
-    ProfScope ps(L, PW_PH_REQUANT, st);
-    hipError_t e = pw::launch_qjobs(b, st);
-    if (e != hipSuccess) return hip_fail(e, "page quantization launch");
-  }
-  return PW_OK;
-}
-
 // Requant of pool pages, grouped by (source, destination) bitwidths in the
 // plan's order, kMaxRqJobs pages per launch. The kernel finds a page's
 // scale/zero block right after its codes (the slot layout of the allocator).
@@ -449,15 +422,27 @@ pw_status pw_layer_load_page(pw_layer* L, int e, int proj, int rb, int bits, con
   if (s != PW_OK) return fail(s, err);
   hipStream_t st = static_cast<hipStream_t>(stream);
   // 16-bit: the rows are laid out as tiles; 8/4-bit: quantized into tiles
+  // (profiled with the requant phase)
+  const pw_layer_desc& d = L->st.desc;
   pw::QJob j{};
-  j.K = L->st.kdim(proj);
   j.src = static_cast<const uint8_t*>(rows16);
   j.dst = L->pool + ent.data_off;
   j.dst_sz = bits == 16 ? nullptr : L->pool + ent.sz_off;
-  j.dst_bits = static_cast<uint8_t>(bits);
-  j.src_plain = 1;
-  s = run_qjobs(L, {j}, st);
-  if (s == PW_OK) s = write_entries(L, {{L->st.index(e, proj, rb), ent}}, st);
+  j.slot = L->table + L->st.index(e, proj, rb);
+  j.ent = ent;
+  j.K = L->st.kdim(proj);
+  j.R = d.R;
+  j.G = d.G;
+  j.act = d.act;
+  j.sdt = d.sdt;
+  j.dst_bits = bits;
+  j.items = static_cast<uint32_t>(d.R / 16) * static_cast<uint32_t>(j.K / std::max(d.G, 128));
+  hipError_t he = hipSuccess;
+  {
+    ProfScope ps(L, PW_PH_REQUANT, st);
+    he = pw::launch_qjob(j, st);
+  }
+  if (he != hipSuccess) s = hip_fail(he, "page quantization launch");
   if (s != PW_OK) {
     drain(st);
     L->st.abort_slot(ent, proj);

@@ -391,19 +391,13 @@ struct QRaw {
   uint32_t sz[4];
 };
 
-// The lane's four 16-byte pieces of 16-bit block blk of row tile tau: from a
-// 16-bit pool page (tile layout) or from R x K row-major rows (src_plain).
+// The lane's four 16-byte pieces of block blk of row tile tau of the source's
+// R x K row-major 16-bit rows.
 __device__ __forceinline__ void q_load(const QJob& job, int tau, int blk, QRaw& raw) {
   const int lane = lane_id(), lc = lane & 15, lg = lane >> 4;
-  const int K = job.K, nkb = K / 128;
-  const size_t tile = static_cast<size_t>(tau) * nkb + blk;
+  const uint8_t* src = job.src + (static_cast<size_t>(tau * 16 + lc) * job.K + blk * 128 + 8 * lg) * 2;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint8_t* src = job.src_plain
-        ? job.src + (static_cast<size_t>(tau * 16 + lc) * K + blk * 128 + 32 * i + 8 * lg) * 2
-        : job.src + tile * 4096 + 1024 * i + 16 * lane;
-    raw.w[i] = *reinterpret_cast<const u32x4*>(src);
-  }
+  for (int i = 0; i < 4; ++i) raw.w[i] = *reinterpret_cast<const u32x4*>(src + 64 * i);
 }
 
 // The 32 values (k-steps i = 0..3, 8 values each) lane l holds of the block,
@@ -568,7 +562,7 @@ __device__ __forceinline__ float q_elem(const QRaw& raw, int e) {
 
 // One 16-bit block quantized to the job's destination (16: layout transform).
 template <int ACT, int SDT, int GK>
-__device__ __forceinline__ void q_block(const QJob& job, const QJobBatch& b, const QRaw& raw, int tau, int blk, int lg,
+__device__ __forceinline__ void q_block(const QJob& job, const QRaw& raw, int tau, int blk, int lg,
                                         int r, int Q) {
   constexpr int SRC = 16;
   const int lane = lane_id();
@@ -627,49 +621,30 @@ __device__ __forceinline__ void q_block(const QJob& job, const QJobBatch& b, con
   }
   if (lg == 0) {
     const int gi = GK == kQG64 ? 2 * blk : blk;
-    *reinterpret_cast<uint32_t*>(job.dst_sz + (static_cast<size_t>(gi) * b.R + r) * 4) = sb0 | (zb0 << 16);
+    *reinterpret_cast<uint32_t*>(job.dst_sz + (static_cast<size_t>(gi) * job.R + r) * 4) = sb0 | (zb0 << 16);
     if (GK == kQG64)
-      *reinterpret_cast<uint32_t*>(job.dst_sz + (static_cast<size_t>(gi + 1) * b.R + r) * 4) = sb1 | (zb1 << 16);
+      *reinterpret_cast<uint32_t*>(job.dst_sz + (static_cast<size_t>(gi + 1) * job.R + r) * 4) = sb1 | (zb1 << 16);
   }
-}
-
-// Work item -> (job j, 16-row tile tau, span sp of max(G, 128) values); job
-// j's items start at job[j].item_base.
-struct QItem {
-  int j, tau, sp;
-};
-__device__ __forceinline__ QItem q_item(const QJobBatch& b, uint32_t item, int span) {
-  QItem it;
-  int j = 0;
-  while (j + 1 < b.n_jobs && item >= b.job[j + 1].item_base) ++j;   // wave-uniform
-  const int nsp = (b.job[j].K / 128) / span;
-  const int rem = static_cast<int>(item - b.job[j].item_base);
-  it.j = j;
-  it.tau = rem / nsp;
-  it.sp = rem % nsp;
-  return it;
 }
 
 // One wave per item: a 16-row tile over one span of K. G <= 128 (every group
 // inside one block): one block, quantized from registers in one pass. G > 128:
 // G / 128 blocks, two passes (the group's extremes, then the codes).
 template <int ACT, int SDT, int GK>
-__device__ __forceinline__ void qjobs_item(const QJobBatch& b) {
+__device__ __forceinline__ void qjob_item(const QJob& job) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *job.slot = job.ent;
   const uint32_t item = blockIdx.x * 4u + (threadIdx.x >> 6);
-  if (item >= b.total_items) return;
+  if (item >= job.items) return;
   const int lane = lane_id(), lc = lane & 15, lg = lane >> 4;
-  const int R = b.R;
-  const int span = GK == kQGBig ? b.G / 128 : 1;    // blocks per item
-  const QItem it = q_item(b, item, span);
-  const QJob& job = b.job[it.j];
-  const int tau = it.tau, sp = it.sp;
+  const int span = GK == kQGBig ? job.G / 128 : 1;    // blocks per item
+  const int nsp = (job.K / 128) / span;
+  const int tau = static_cast<int>(item) / nsp, sp = static_cast<int>(item) % nsp;
   const int r = tau * 16 + lc;
   const int Q = (1 << job.dst_bits) - 1;
   if constexpr (GK != kQGBig) {
     QRaw raw;
     q_load(job, tau, sp, raw);
-    q_block<ACT, SDT, GK>(job, b, raw, tau, sp, lg, r, Q);
-    (void)R;
+    q_block<ACT, SDT, GK>(job, raw, tau, sp, lg, r, Q);
   } else {
     float v[32];
     if (job.dst_bits == 16) {
@@ -691,20 +666,20 @@ __device__ __forceinline__ void qjobs_item(const QJobBatch& b) {
       q_read<ACT>(job, tau, blk, v);
       q_store_codes<SDT, GK>(job, tau, blk, v, sb0, zb0, 0u, 0u, Q);
     }
-    if (lg == 0) *reinterpret_cast<uint32_t*>(job.dst_sz + (static_cast<size_t>(sp) * R + r) * 4) = sb0 | (zb0 << 16);
+    if (lg == 0) *reinterpret_cast<uint32_t*>(job.dst_sz + (static_cast<size_t>(sp) * job.R + r) * 4) = sb0 | (zb0 << 16);
   }
 }
 
 template <int ACT, int SDT, int GK>
-__global__ __launch_bounds__(256) void k_qjobs(const QJobBatch b) {
-  qjobs_item<ACT, SDT, GK>(b);
+__global__ __launch_bounds__(256) void k_qjob(const QJob job) {
+  qjob_item<ACT, SDT, GK>(job);
 }
 
 // G = 128 (one group per block): the one-block path fits in 64 VGPRs, so
 // eight waves per SIMD and 32 blocks per CU are in flight.
 template <int ACT, int SDT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_qjobs_g128(const QJobBatch b) {
-  qjobs_item<ACT, SDT, kQG128>(b);
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_qjob_g128(const QJob job) {
+  qjob_item<ACT, SDT, kQG128>(job);
 }
 
 // ---------------------------------------------------------------------------
@@ -1492,21 +1467,21 @@ hipError_t launch_permute(const int32_t* ids, int T, int K, int E, int32_t* offs
 }
 
 template <int ACT, int SDT>
-static void qjobs_go(const QJobBatch& b, hipStream_t st) {
-  const dim3 grid((b.total_items + 3) / 4), block(256);
-  if (b.G == 64) hipLaunchKernelGGL((k_qjobs<ACT, SDT, kQG64>), grid, block, 0, st, b);
-  else if (b.G == 128) hipLaunchKernelGGL((k_qjobs_g128<ACT, SDT>), grid, block, 0, st, b);
-  else hipLaunchKernelGGL((k_qjobs<ACT, SDT, kQGBig>), grid, block, 0, st, b);
+static void qjob_go(const QJob& job, hipStream_t st) {
+  const dim3 grid((job.items + 3) / 4), block(256);
+  if (job.G == 64) hipLaunchKernelGGL((k_qjob<ACT, SDT, kQG64>), grid, block, 0, st, job);
+  else if (job.G == 128) hipLaunchKernelGGL((k_qjob_g128<ACT, SDT>), grid, block, 0, st, job);
+  else hipLaunchKernelGGL((k_qjob<ACT, SDT, kQGBig>), grid, block, 0, st, job);
 }
 
-hipError_t launch_qjobs(const QJobBatch& b, hipStream_t st) {
-  if (b.total_items == 0) return hipSuccess;
-  if (b.act == PW_BF16) {
-    if (b.sdt == PW_BF16) qjobs_go<PW_BF16, PW_BF16>(b, st);
-    else qjobs_go<PW_BF16, PW_F16>(b, st);
+hipError_t launch_qjob(const QJob& job, hipStream_t st) {
+  if (job.items == 0) return hipErrorInvalidValue;
+  if (job.act == PW_BF16) {
+    if (job.sdt == PW_BF16) qjob_go<PW_BF16, PW_BF16>(job, st);
+    else qjob_go<PW_BF16, PW_F16>(job, st);
   } else {
-    if (b.sdt == PW_BF16) qjobs_go<PW_F16, PW_BF16>(b, st);
-    else qjobs_go<PW_F16, PW_F16>(b, st);
+    if (job.sdt == PW_BF16) qjob_go<PW_F16, PW_BF16>(job, st);
+    else qjob_go<PW_F16, PW_F16>(job, st);
   }
   return hipGetLastError();
 }
