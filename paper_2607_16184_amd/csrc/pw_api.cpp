@@ -193,6 +193,23 @@ RangePlan plan_range(const pw_layer_desc& d, int e0, int ne, size_t S, size_t S_
   return r;
 }
 
+// 16-row weight tiles per wave of the decode kernels at one or two slot tiles
+// per pass (the bits are the same either way). Two halve the LDS operand
+// reads and the activation staging per weight byte, which is what waves on 8-
+// and 4-bit pages spend their issue slots on; waves on 16-bit pages wait for
+// memory, and there half as many, longer workgroups balance worse. So two
+// where at most an eighth of the pages are 16-bit, every expert expects a slot
+// and the workgroups still cover the chip. Measured, one / two (us a step): 8
+// experts of 4096 x 14336, 64 tokens, no 16-bit page 239 / 209, 12 % 267 / 251,
+// 25 % 300 / 291, 50 % 359 / 366; 33 tokens 216 / 204; one token (two experts)
+// 61 / 65; 64 experts of 2048 x 1408, 100 tokens, no 16-bit page 103 / 92;
+// 60 + 4 experts, 128 tokens, 25 % 164 / 165; 8 experts of 2048 x 4096, 16
+// tokens, no 16-bit page 47 / 42.
+int row_tiles(const pw::LayerState& st, const RangePlan& r) {
+  const size_t ne = static_cast<size_t>(r.ne);
+  return st.n_16 * 8 <= st.n_pages && r.S >= ne && ne * (st.desc.F / 64) >= kCUs ? 2 : 1;
+}
+
 WsLayout ws_layout(const pw_layer_desc& d, int T, int K, bool apl, int n_shared) {
   WsLayout w{};
   const size_t S = static_cast<size_t>(T) * K;
@@ -723,6 +740,7 @@ pw_status pw_moe_paged_gemm(const pw_layer* Lc, const void* x, int T, int K, con
     a.nsplit = r.nsplit;
     a.kb_per_split = r.kb_per_split;
     a.mtb = r.mtb;
+    a.rt = row_tiles(L->st, r);
   };
   const char* what = nullptr;
   {

@@ -16,10 +16,19 @@
 // as an exact 16-bit float (int8 codes through an exact conversion; int4
 // codes, and int8 codes with fp16 activations, OR-ed into the mantissa of a
 // constant OFF, giving OFF + c exactly). Per group of G along K the MFMA gives
-// P = sum (c + OFF) x, and X = sum x comes from sums taken while the
-// activations are staged; the group's scale s and zero z are then applied in
-// fp32 on the accumulator: acc += s * P + (z - OFF * s) * X, which is
-// sum (z + c s) x. Weights are never rounded: z + c*s enters exactly.
+// P = sum (c + OFF) x and X = sum x; the group's scale s and zero z are then
+// applied in fp32 on the accumulator: acc += s * P + (z - OFF * s) * X, which
+// is sum (z + c s) x. Weights are never rounded: z + c*s enters exactly.
+//
+// X. With one or two slot tiles per pass, X is one more MFMA per k-step, an
+// operand of ones against the activations already read for P (every row of
+// the result is the slot's sum, the layout the correction needs); it replaces
+// dot products, cross-lane sums, LDS writes and reads that cost an int4 wave
+// about a fifth of its instructions (all pages int4, 64 tokens on 8 experts
+// of 4096 x 14336: gate/up 143 -> 135 us, down 78 -> 73; half the pages at 16
+// bits: 229 -> 227). With more slot tiles the extra accumulators cost more
+// (64 experts, 512 tokens: gate/up 100 -> 102 us): X comes from sums taken
+// while the activations are staged.
 #include "pw_device.hpp"
 #include "pw_internal.hpp"
 
@@ -48,6 +57,17 @@ __device__ __forceinline__ float hi16(uint32_t h) {
   if constexpr (FMT == PW_BF16) return __uint_as_float(h & 0xFFFF0000u);
   else return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(h >> 16)));
 }
+
+// A slot tile's activation sum X: an MFMA accumulator (up to two slot tiles
+// per pass) or a sum read from the staged chunk (see the file comment).
+template <int NT> constexpr bool mfma_sums() { return NT <= 2; }
+template <bool M> struct XSum { typedef f32x4 type; };
+template <> struct XSum<false> { typedef float type; };
+template <int NT> using xsum_t = typename XSum<mfma_sums<NT>()>::type;
+__device__ __forceinline__ float xsum_val(f32x4 x) { return x[0]; }
+__device__ __forceinline__ float xsum_val(float x) { return x; }
+__device__ __forceinline__ void xsum_clear(f32x4& x) { x = f32x4{0.f, 0.f, 0.f, 0.f}; }
+__device__ __forceinline__ void xsum_clear(float& x) { x = 0.0f; }
 
 template <int B> struct WF;
 template <> struct WF<16> { u32x4 v[4]; };
@@ -103,10 +123,10 @@ __device__ __forceinline__ u32x4 wf_op(const WF<B>& f, int i, uint32_t magic) {
 template <int ACT> constexpr uint32_t code_magic() { return ACT == PW_BF16 ? 0x43004300u : 0x64006400u; }
 
 // acc += s * P + (z - OFF s) * X for the lane's four rows (two fused
-// multiply-adds per row). X[t] is the group's activation sum for this lane's
-// slot (tile t).
+// multiply-adds per row). xs[t] is the group's activation sum X for this
+// lane's slot (tile t).
 template <int ACT, int SDT, int B, int NT>
-__device__ __forceinline__ void group_fix(f32x4 (&acc)[NT], const f32x4 (&p)[NT], const float (&xs)[NT], u32x4 sz) {
+__device__ __forceinline__ void group_fix(f32x4 (&acc)[NT], const f32x4 (&p)[NT], const xsum_t<NT> (&xs)[NT], u32x4 sz) {
   constexpr float off = CodeOff<ACT, B>::value;
   float s[4], zp[4];
 #pragma unroll
@@ -119,7 +139,7 @@ __device__ __forceinline__ void group_fix(f32x4 (&acc)[NT], const f32x4 (&p)[NT]
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       acc[t][r] = __builtin_fmaf(s[r], p[t][r], acc[t][r]);
-      acc[t][r] = __builtin_fmaf(zp[r], xs[t], acc[t][r]);
+      acc[t][r] = __builtin_fmaf(zp[r], xsum_val(xs[t]), acc[t][r]);
     }
   }
 }
@@ -139,17 +159,16 @@ __device__ __forceinline__ void group_fix(f32x4 (&acc)[NT], const f32x4 (&p)[NT]
 constexpr int kCK = 2;                            // 128-blocks per chunk
 constexpr int kXRow = kCK * 128 * 2 + 16;         // LDS bytes per staged activation row
 
-// Per chunk buffer: NT*16 staged rows, then NT*16 x (2 kCK) fp32 sums of
-// 64-value half blocks (the code-domain X of each quantization group).
+// Per chunk buffer: NT*16 staged rows, then (without MFMA sums) NT*16 x
+// (2 kCK) fp32 sums of 64-value half blocks (the X of each group).
 template <int NT>
-constexpr int xbuf_bytes() { return NT * 16 * kXRow + NT * 16 * 2 * kCK * 4; }
+constexpr int xbuf_bytes() { return NT * 16 * kXRow + (mfma_sums<NT>() ? 0 : NT * 16 * 2 * kCK * 4); }
 template <int NT>
 constexpr int lds_x_bytes() { return 2 * xbuf_bytes<NT>(); }
 
 // A wave streams RT 16-row weight tiles: each B fragment read from LDS feeds
-// RT MFMAs. RT = 1 for up to two slot tiles per expert (decode), RT = 2 for
-// four (the LDS operand traffic per weight byte halves).
-template <int NTMAX> constexpr int row_tiles() { return NTMAX >= 4 ? 2 : 1; }
+// RT MFMAs. RT = 2 for four slot tiles per pass (the LDS operand traffic per
+// weight byte halves); for one or two, the host chooses (GemmArgs::rt).
 
 // Rolling register window of a wave's page: slot j holds one 128-block of the
 // wave's RT row tiles (and their scale/zero pairs for quantized pages).
@@ -255,16 +274,16 @@ __device__ __forceinline__ float sum8(float v) {
   return v;
 }
 
-// Writes the staged rows and, when a quantized page reads them, per row the
-// sums of each 64-value half block (8 consecutive pieces held by 8
-// consecutive lanes).
+// Writes the staged rows and, when a quantized page reads them and X is not an
+// MFMA result, per row the sums of each 64-value half block (8 consecutive
+// pieces held by 8 consecutive lanes).
 template <int ACT, int NT, int NW>
 __device__ __forceinline__ void x_store(const XStage<NT, NW>& s, uint8_t* buf, bool sums) {
   const int col = threadIdx.x % kPieces;
 #pragma unroll
   for (int j = 0; j < x_passes<NT, NW>(); ++j)
     *reinterpret_cast<u32x4*>(buf + x_row<NW>(j) * kXRow + col * 16) = s.v[j];
-  if (sums) {
+  if (!mfma_sums<NT>() && sums) {
     float* hs = reinterpret_cast<float*>(buf + NT * 16 * kXRow);
 #pragma unroll
     for (int j = 0; j < x_passes<NT, NW>(); ++j) {
@@ -288,7 +307,7 @@ __device__ __forceinline__ void lds_barrier() {
 template <int ACT, int SDT, int B, int NT, int GK, int RT>
 __device__ __forceinline__ void compute_block(const Slot<B, GK, RT>& sl, const uint8_t* xblk, const float* hsum,
                                               int hb0, bool gend, uint32_t magic, f32x4 (&acc)[RT][NT],
-                                              f32x4 (&p)[RT][NT], float (&xs)[NT]) {
+                                              f32x4 (&p)[RT][NT], xsum_t<NT> (&xs)[NT]) {
   const int lane = lane_id(), lc = lane & 15, lg = lane >> 4;
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -305,12 +324,14 @@ __device__ __forceinline__ void compute_block(const Slot<B, GK, RT>& sl, const u
         if constexpr (B == 16) acc[rt][t] = mma<ACT>(aw[rt], bx, acc[rt][t]);
         else p[rt][t] = mma<ACT>(aw[rt], bx, fresh ? zero : p[rt][t]);
       }
+      if constexpr (B != 16 && mfma_sums<NT>()) xs[t] = mma<ACT>(ones_op<ACT>(), bx, fresh ? zero : xs[t]);
     }
     if constexpr (B != 16) {
       if constexpr (GK == kG64) {
         if (i & 1) {
 #pragma unroll
-          for (int t = 0; t < NT; ++t) xs[t] = hsum[(t * 16 + lc) * (2 * kCK) + hb0 + (i >> 1)];
+          for (int t = 0; t < NT; ++t)
+            if constexpr (!mfma_sums<NT>()) xs[t] = hsum[(t * 16 + lc) * (2 * kCK) + hb0 + (i >> 1)];
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) group_fix<ACT, SDT, B, NT>(acc[rt], p[rt], xs, sl.sz[rt][i >> 1]);
         }
@@ -318,14 +339,15 @@ __device__ __forceinline__ void compute_block(const Slot<B, GK, RT>& sl, const u
         if (i == 3) {
 #pragma unroll
           for (int t = 0; t < NT; ++t)
-            xs[t] = hsum[(t * 16 + lc) * (2 * kCK) + hb0] + hsum[(t * 16 + lc) * (2 * kCK) + hb0 + 1];
+            if constexpr (!mfma_sums<NT>())
+              xs[t] = hsum[(t * 16 + lc) * (2 * kCK) + hb0] + hsum[(t * 16 + lc) * (2 * kCK) + hb0 + 1];
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) group_fix<ACT, SDT, B, NT>(acc[rt], p[rt], xs, sl.sz[rt][0]);
         }
       } else if (i == 3) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
-          xs[t] += hsum[(t * 16 + lc) * (2 * kCK) + hb0] + hsum[(t * 16 + lc) * (2 * kCK) + hb0 + 1];
+          if constexpr (!mfma_sums<NT>()) xs[t] += hsum[(t * 16 + lc) * (2 * kCK) + hb0] + hsum[(t * 16 + lc) * (2 * kCK) + hb0 + 1];
         if (gend) {
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) {
@@ -334,7 +356,7 @@ __device__ __forceinline__ void compute_block(const Slot<B, GK, RT>& sl, const u
             for (int t = 0; t < NT; ++t) p[rt][t] = zero;
           }
 #pragma unroll
-          for (int t = 0; t < NT; ++t) xs[t] = 0.0f;
+          for (int t = 0; t < NT; ++t) xsum_clear(xs[t]);
         }
       }
     }
@@ -360,12 +382,12 @@ __device__ void wave_gemm(uint8_t* lds, const uint8_t* xbase, const uint32_t (&r
   uint32_t magic = code_magic<ACT>();
   asm volatile("" : "+v"(magic));
   f32x4 p[RT][NT];
-  float xs[NT];
+  xsum_t<NT> xs[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) acc[rt][t] = p[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    xs[t] = 0.0f;
+    xsum_clear(xs[t]);
   }
   Slot<B, GK, RT> win[W];
   XStage<NT, NW> xr;
@@ -538,9 +560,8 @@ __device__ __forceinline__ int xcd_expert_order(int b, int per_e, int ne) {
 
 // NTMAX slot tiles per pass (1, 2 or 4); experts with fewer slots take fewer
 // (at NTMAX = 4 also three).
-template <int ACT, int SDT, int NTMAX, int GK, int NW>
+template <int ACT, int SDT, int NTMAX, int GK, int NW, int RT>
 __global__ __launch_bounds__(64 * NW) void k_gateup(const GemmArgs a) {
-  constexpr int RT = row_tiles<NTMAX>();
   constexpr int GU = gu_rows<RT, NW>();
   __shared__ __attribute__((aligned(16))) uint8_t lds[gu_lds_bytes<NTMAX, RT, NW>()];
   const int upe = a.F / GU;
@@ -621,9 +642,8 @@ __device__ __forceinline__ void down_any(int code, const GemmArgs& a, uint8_t* l
   }
 }
 
-template <int ACT, int SDT, int NTMAX, int GK, int NW>
+template <int ACT, int SDT, int NTMAX, int GK, int NW, int RT>
 __global__ __launch_bounds__(64 * NW) void k_down(const GemmArgs a) {
-  constexpr int RT = row_tiles<NTMAX>();
   constexpr int DN = dn_rows<RT, NW>();
   __shared__ __attribute__((aligned(16))) uint8_t lds[lds_x_bytes<NTMAX>()];
   const int upe = a.H / DN;
@@ -655,25 +675,30 @@ __global__ __launch_bounds__(64 * NW) void k_down(const GemmArgs a) {
 // larger units, else 4.
 template <int NTMAX> constexpr int waves_for() { return NTMAX == 4 ? 8 : 4; }
 
-template <int ACT, int SDT, int GK, int NTMAX, int NW>
+template <int ACT, int SDT, int GK, int NTMAX, int NW, int RT>
 void gemm_launch_nw(const GemmArgs& a, bool gateup, hipStream_t st) {
-  constexpr int RT = row_tiles<NTMAX>();
   const dim3 block(64 * NW);
   if (gateup)
-    hipLaunchKernelGGL((k_gateup<ACT, SDT, NTMAX, GK, NW>), dim3(a.ne * (a.F / gu_rows<RT, NW>())), block, 0, st, a);
+    hipLaunchKernelGGL((k_gateup<ACT, SDT, NTMAX, GK, NW, RT>), dim3(a.ne * (a.F / gu_rows<RT, NW>())), block, 0, st,
+                       a);
   else
-    hipLaunchKernelGGL((k_down<ACT, SDT, NTMAX, GK, NW>), dim3(a.ne * (a.H / dn_rows<RT, NW>()) * a.nsplit), block, 0,
-                       st, a);
+    hipLaunchKernelGGL((k_down<ACT, SDT, NTMAX, GK, NW, RT>), dim3(a.ne * (a.H / dn_rows<RT, NW>()) * a.nsplit), block,
+                       0, st, a);
 }
 
 template <int ACT, int SDT, int GK, int NTMAX>
 void gemm_launch_nt(const GemmArgs& a, bool gateup, hipStream_t st) {
-  constexpr int RT = row_tiles<NTMAX>();
-  constexpr int NW = waves_for<NTMAX>();
-  if (NW != 4 && a.F % gu_rows<RT, NW>() == 0 && a.H % dn_rows<RT, NW>() == 0)
-    gemm_launch_nw<ACT, SDT, GK, NTMAX, NW>(a, gateup, st);
-  else
-    gemm_launch_nw<ACT, SDT, GK, NTMAX, 4>(a, gateup, st);
+  if constexpr (NTMAX == 4) {
+    constexpr int NW = waves_for<NTMAX>();
+    if (a.F % gu_rows<2, NW>() == 0 && a.H % dn_rows<2, NW>() == 0)
+      gemm_launch_nw<ACT, SDT, GK, NTMAX, NW, 2>(a, gateup, st);
+    else
+      gemm_launch_nw<ACT, SDT, GK, NTMAX, 4, 2>(a, gateup, st);
+  } else if (a.rt == 2) {
+    gemm_launch_nw<ACT, SDT, GK, NTMAX, 4, 2>(a, gateup, st);
+  } else {
+    gemm_launch_nw<ACT, SDT, GK, NTMAX, 4, 1>(a, gateup, st);
+  }
 }
 
 template <int ACT, int SDT, int GK>

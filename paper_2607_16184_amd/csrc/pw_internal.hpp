@@ -92,6 +92,7 @@ struct GemmArgs {
   int out_fp32;
   int act, sdt;
   int mtb;                    // M tiles (of 16 slots) per pass: 1, 2 or 4
+  int rt;                     // 16-row weight tiles per wave at one or two M tiles: 1 or 2
   int apl;                    // the layer holds nested bit-plane pages
   // experts [e0, e0 + ne) are the ones a GEMM launch covers, holding about
   // s_range of the S slots (routed and shared experts run as separate launches)

@@ -138,6 +138,7 @@ void LayerState::finish_load(int e, int proj, int rb, const pw_page_entry& ent) 
   mirror[index(e, proj, rb)] = ent;
   ++n_present;
   if ((ent.rsv & 0xFF) == PW_FMT_APL) ++n_apl;
+  if (ent.bits == 16) ++n_16;
 }
 
 void LayerState::abort_slot(const pw_page_entry& ent, int proj) {
@@ -211,6 +212,7 @@ void LayerState::committed(void* commit_ev) {
       retired_.push_back(Retired{cur.data_off, entry_bytes(p.proj, cur), commit_ev});
     }
     ref_event(commit_ev);
+    n_16 += (p.next.bits == 16 ? 1 : 0) - (cur.bits == 16 ? 1 : 0);
     cur = published(p.next);
     unref_event(p.ev);
   }

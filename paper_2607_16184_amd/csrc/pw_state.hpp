@@ -105,6 +105,7 @@ class LayerState {
     return e;
   }
   size_t n_apl = 0;                // present nested bit-plane pages
+  size_t n_16 = 0;                 // committed 16-bit pages
 
   bool check_block(int e, int proj, int rb, std::string* err) const;
   bool all_present() const { return n_present == n_pages; }

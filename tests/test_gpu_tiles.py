@@ -5,7 +5,9 @@ units), short reductions and mixed page formats, against the CPU oracle.
 The kernel multiplies quantized weights rounded to the activation dtype
 (w_round) and rounds the SwiGLU output there too; what is left between the
 two is the order of fp32 sums over K <= 640 products, far below the 1e-3
-allowed (the bound the other fp32 parity tests use).
+allowed (the bound the other fp32 parity tests use). The decode kernels'
+two-row-tile form (layers with few 16-bit pages) keeps weights exact, so it
+is held to the same bound against the plain oracle.
 """
 import dataclasses
 
@@ -47,5 +49,29 @@ def test_tile_edges(counts, H, F, R, G, act, sdt):
     ids, w = oracle.route(lg, 1)
     assert np.array_equal(np.bincount(ids[:, 0], minlength=E), counts)
     e = rel_err(y.cpu().numpy(), O.forward(x16, ids, w, h_round=True, w_round=True))
+    assert e <= 1e-3, e
+    L.close()
+
+
+@pytest.mark.parametrize("T,share16,H,G,act,sdt", [
+    (16, 0.0, 256, 64, F16, F16),        # one slot tile per pass
+    (60, 0.12, 256, 128, BF16, BF16),    # two, an eighth of the pages at 16 bits
+    (33, 0.0, 512, 256, BF16, F16),      # groups over two 128-blocks
+    (16, 0.0, 384, 128, F16, BF16),      # an odd number of 128-blocks
+])
+def test_decode_two_row_tiles(T, share16, H, G, act, sdt):
+    import torch
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], H=H, F=2048, R=64, G=G, T=T, act=act, sdt=sdt,
+                              mix=(share16, 0.4, 0.6 - share16))
+    w16 = [synth.expert_weights(cfg, p) for p in range(3)]
+    bits = synth.bitmap(cfg)
+    say("two row tiles T=%d H=%d G=%d act=%d" % (T, H, G, act))
+    L = gpu_layer(cfg, w16, bits, synth.pool_order(cfg))
+    O = oracle_layer(cfg, w16, bits)
+    lg, x16 = synth.logits(cfg), synth.activations(cfg)
+    y = L.forward(to_dev16(x16), L.route(to_dev(lg), cfg.K), out_fp32=True)
+    torch.cuda.synchronize()
+    ids, w = oracle.route(lg, cfg.K)
+    e = rel_err(y.cpu().numpy(), O.forward(x16, ids, w, h_round=True))
     assert e <= 1e-3, e
     L.close()
