@@ -143,11 +143,16 @@ __global__ __launch_bounds__(256) void k_route_topk(const float* __restrict__ lo
 }
 
 // Token permutation, one workgroup per expert e. Each workgroup builds the
-// full histogram (order-free LDS atomics on counts), so every expert's offset
-// is known everywhere; wave q then owns the q-th quarter of the slots and
-// places e's slots in it in slot order: a ballot per 64 slots gives the ranks,
-// the counts of the earlier quarters the base. No order depends on timing.
-constexpr int kPermThreads = 256;
+// full histogram (order-free LDS atomics on counts), so its expert's offset is
+// known from a sum over the earlier experts' counts; wave q then owns the q-th
+// sixteenth of the slots and places e's slots in it in slot order: a ballot
+// per 64 slots gives the ranks, the counts of the earlier waves the base. No
+// order depends on timing. The kernel is bound by the length of each thread's
+// pass over the slots, so a workgroup has 16 waves (4 waves and serial sums
+// over the counts: 23.6 us at 24576 slots x 64 experts, now 10.5; 8192 x 8: 9.8,
+// now 8.7).
+constexpr int kPermThreads = 1024;
+constexpr int kPermWaves = kPermThreads / 64;
 constexpr int kMaxExperts = 256;
 
 // Ballots of `e` over slots [q0, q1) in 8-block steps (loads in flight
@@ -183,7 +188,7 @@ __global__ __launch_bounds__(kPermThreads) void k_permute(const int32_t* __restr
                                                           int32_t* __restrict__ sorted_slot,
                                                           int32_t* __restrict__ slot_pos) {
   __shared__ int cnt[kMaxExperts];
-  __shared__ int qcnt[4];
+  __shared__ int qcnt[kPermWaves];
   const int e = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
   for (int i = tid; i < E; i += kPermThreads) cnt[i] = 0;
   __syncthreads();
@@ -199,21 +204,19 @@ __global__ __launch_bounds__(kPermThreads) void k_permute(const int32_t* __restr
     for (int j = 0; j < 8; ++j)
       if (id[j] >= 0 && id[j] < E) atomicAdd(&cnt[id[j]], 1);
   }
-  const int per = ((S + 3) / 4 + 63) / 64 * 64;
+  const int per = ((S + kPermWaves - 1) / kPermWaves + 63) / 64 * 64;
   const int q0 = min(S, wave * per), q1 = min(S, q0 + per);
   const int mine = perm_scan(ids, q0, q1, e, [](int, int) {});
   if (lane == 0) qcnt[wave] = mine;
   __syncthreads();
-  if (e == 0 && tid == 0) {
-    int acc = 0;
-    for (int x = 0; x < E; ++x) {
-      offsets[x] = acc;
-      acc += cnt[x];
-    }
-    offsets[E] = acc;
-  }
   int base = 0;
-  for (int x = 0; x < e; ++x) base += cnt[x];
+  for (int x = lane; x < e; x += 64) base += cnt[x];
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) base += __shfl_xor(base, m);
+  if (tid == 0) {
+    offsets[e] = base;
+    if (e == E - 1) offsets[E] = base + cnt[e];
+  }
   for (int w = 0; w < wave; ++w) base += qcnt[w];
   perm_scan(ids, q0, q1, e, [&](int s, int r) {
     sorted_slot[base + r] = s;
