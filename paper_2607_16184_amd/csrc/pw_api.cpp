@@ -217,11 +217,24 @@ WsLayout ws_layout(const pw_layer_desc& d, int T, int K, bool apl, int n_shared)
   w.r[0] = plan_range(d, 0, d.E - n_shared, S - S_sh, S, apl);
   w.r[1] = plan_range(d, d.E - n_shared, n_shared, S_sh, S, apl);
   auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-  w.h_off = 0;
-  w.h_bytes = al(S * d.F * 2);
-  w.op_off = w.h_bytes;
-  w.op_bytes = al(static_cast<size_t>(std::max(w.r[0].nsplit, w.r[1].nsplit)) * S * d.H * 4);
-  w.total = w.h_bytes + w.op_bytes;
+  auto place = [&]() {
+    w.h_off = 0;
+    w.h_bytes = al(S * d.F * 2);
+    w.op_off = w.h_bytes;
+    w.op_bytes = al(static_cast<size_t>(std::max(w.r[0].nsplit, w.r[1].nsplit)) * S * d.H * 4);
+    w.total = w.h_bytes + w.op_bytes;
+  };
+  place();
+  // Narrow slot tiles split the down projection only where the partials leave
+  // the call within the static workspace of the allocation-free entry point.
+  if (w.total > pw::kStaticScratchBytes) {
+    for (RangePlan& r : w.r) {
+      if (r.ne <= 0 || r.path != GemmPath::kTiled || (r.S + r.ne - 1) / r.ne >= 128) continue;
+      r.nsplit = 1;
+      r.kb_per_split = d.F / 128;
+    }
+    place();
+  }
   return w;
 }
 

@@ -75,3 +75,50 @@ def test_decode_two_row_tiles(T, share16, H, G, act, sdt):
     e = rel_err(y.cpu().numpy(), O.forward(x16, ids, w, h_round=True))
     assert e <= 1e-3, e
     L.close()
+
+
+def test_narrow_tiles_keep_within_static_workspace():
+    """100 slots per expert, 3200 slots of H = 4096: the SwiGLU rows and one copy
+    of the down partials fit the allocation-free entry point's 64 MiB, two
+    copies would not, so the call is taken with one and gives the same bits as
+    with a workspace of the caller's."""
+    import torch
+    from paper_2607_16184_amd import pw
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], E=32, K=1, H=4096, F=128, T=3200, act=BF16, sdt=BF16)
+    say("narrow tiles in the static workspace")
+    L = gpu_layer(cfg, [synth.expert_weights(cfg, p) for p in range(3)], synth.bitmap(cfg), synth.pool_order(cfg))
+    one = cfg.T * (cfg.F * 2 + cfg.H * 4)
+    assert one <= 64 << 20 < one + cfg.T * cfg.H * 4
+    assert pw.pw_workspace_bytes(L.handle, cfg.T, 1) <= 64 << 20
+    x = to_dev16(synth.activations(cfg))
+    routing = L.route(to_dev(synth.logits(cfg)), 1)
+    want = L.forward(x, routing, out_fp32=True)
+    y = torch.full_like(want, float("nan"))
+    _, w, off, ss, sp = routing
+    pw.pw_moe_paged_gemm_noalloc(L.handle, x.data_ptr(), cfg.T, 1, w.data_ptr(), off.data_ptr(), ss.data_ptr(),
+                                 sp.data_ptr(), y.data_ptr(), 1, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(y, want)
+    L.close()
+
+
+def test_swiglu_over_the_exponent_range():
+    """Gate values of a few hundred either way: exp(-g) overflows, vanishes and
+    passes through everything between; the output keeps the usual bound."""
+    import torch
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], K=1, T=600, act=BF16, sdt=BF16)
+    w16 = [synth.expert_weights(cfg, p) for p in range(3)]
+    bits = synth.bitmap(cfg)
+    say("swiglu over the exponent range")
+    L = gpu_layer(cfg, w16, bits, synth.pool_order(cfg))
+    O = oracle_layer(cfg, w16, bits)
+    lg = synth.logits(cfg)
+    x16 = synth.to16(300.0 * synth.from16(synth.activations(cfg), BF16), BF16)   # g ~ N(0, 96)
+    y = L.forward(to_dev16(x16), L.route(to_dev(lg), 1), out_fp32=True)
+    torch.cuda.synchronize()
+    ids, w = oracle.route(lg, 1)
+    got = y.cpu().numpy()
+    assert np.isfinite(got).all()
+    e = rel_err(got, O.forward(x16, ids, w, h_round=True, w_round=True))
+    assert e <= 1e-3, e
+    L.close()
