@@ -556,15 +556,18 @@ __device__ __forceinline__ bool find_tile(const GemmArgs& a, int nblk, int* e_ou
 // hides (a tile's 64 elements per lane took 4 of about 110 us); here exp(-g) is
 // exp2 of -g log2(e) with that product's rounding error put back as a factor,
 // and the quotient a reciprocal with one Newton step, each within an ulp or
-// two. The exponent is held at 2^127, where the reciprocal (a denormal) is 0.
+// two. g enters the exponent held to +-90, beyond which exp(-g) is infinite
+// (the quotient then g * 0) or below half an ulp of 1; g itself, infinite or
+// not, enters the product.
 __device__ __forceinline__ float swiglu(float g, float u) {
-  const float t = g * -1.44269504f;
-  const float err = __builtin_fmaf(g, -1.44269504f, -t) + g * -1.92596303e-8f;
-  const float e = __builtin_amdgcn_exp2f(fminf(t, 127.0f)) * __builtin_fmaf(err, 0.693147182f, 1.0f);
+  const float x = __builtin_amdgcn_fmed3f(g, -90.0f, 90.0f);
+  const float t = x * -1.44269504f;
+  const float err = __builtin_fmaf(x, -1.44269504f, -t) + x * -1.92596303e-8f;
+  const float e = __builtin_amdgcn_exp2f(t) * __builtin_fmaf(err, 0.693147182f, 1.0f);
   const float d = 1.0f + e;
-  float r = __builtin_amdgcn_rcpf(d);
-  r = __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
-  return g * r * u;
+  const float r = __builtin_amdgcn_rcpf(d);
+  const float r1 = __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
+  return g * (d < 0x1p126f ? r1 : r) * u;
 }
 
 template <int ACT, int SDT, bool GATEUP, int TM>
