@@ -1,0 +1,191 @@
+// The plan of a paged GEMM call: which kernels serve its expert ranges, how the
+// down projection is split, the workspace that takes, and whether work is
+// forked to the layer's own stream. Pure functions of the layer's shape, its
+// page counts and the batch: no HIP, so that the rules run on the CPU as well.
+#pragma once
+
+#include <algorithm>
+#include <cstddef>
+#include <cstdint>
+
+#include "pw.h"
+
+namespace pw {
+
+// Capacity of the static device scratch of the allocation-free GEMM entry point.
+constexpr size_t kStaticScratchBytes = size_t(64) << 20;
+
+// Device workspace layout of pw_moe_paged_gemm.
+enum class GemmPath { kDecode, kStream, kTiled };
+
+// One expert range of a call, run by its own GEMM launches: the routed
+// experts [0, E - n_shared), and the shared experts (the last n_shared, each
+// used by every token). Its kernel path, the decode kernels' slot tiles per
+// pass and the down projection's K splits follow the range's own slots.
+struct RangePlan {
+  int e0, ne;          // experts [e0, e0 + ne)
+  size_t S;            // slots routed to them
+  GemmPath path;
+  int nsplit, kb_per_split, mtb;
+};
+
+struct WsLayout {
+  size_t h_off, h_bytes, op_off, op_bytes, total;
+  RangePlan r[2];      // routed, shared (ne = 0 without shared experts)
+};
+
+// Which GEMM kernels serve a range, from its expected slots per expert
+// S / ne: up to 48, the decode kernels (weights streamed in registers, exact
+// code-domain arithmetic, up to four 16-slot tiles per pass); above, the
+// LDS-tiled kernel (256 weight rows x 128 or 256 slots; at 55, 75 and 105
+// slots per expert of 4096 x 14336 it takes 441, 490 and 500 us a step, the
+// streaming kernel 493, 641 and 664 us). The streaming kernel (64-slot tiles)
+// serves bit-plane layers and shapes whose down projection is not a multiple
+// of 256 rows. The shared experts of a decode-sized batch are a few experts with a
+// few hundred slots each: where the tiled kernel's tiles would not give every
+// CU a workgroup, the streaming kernel's smaller tiles spread their work. The
+// last two need 32/64-row staging inside one page, 128-row down blocks and
+// 32-bit activation row offsets (and the tiled kernel 256-row down blocks).
+constexpr size_t kCUs = 256;
+
+inline GemmPath pick_path(const pw_layer_desc& d, size_t S, size_t S_all, int ne, bool apl, bool shared) {
+  const size_t expect = (S + ne - 1) / ne;
+  const bool fits = S_all * d.F * 2 < (size_t(1) << 32) && S_all * d.H * 2 < (size_t(1) << 32);
+  const bool tiles = fits && d.G >= 64 && d.R % 64 == 0 && d.F % 128 == 0;
+  // nested bit-plane pages are read by the streaming kernel only
+  if (apl) return GemmPath::kStream;
+  if (expect > 48 && tiles && d.H % 256 == 0) {
+    const size_t tiled_wgs = static_cast<size_t>(ne) * ((expect + 255) / 256) * (d.F / 128);
+    return shared && tiled_wgs < kCUs ? GemmPath::kStream : GemmPath::kTiled;
+  }
+  if (expect > 48 && tiles && d.H % 128 == 0) return GemmPath::kStream;
+  return GemmPath::kDecode;
+}
+
+inline RangePlan plan_range(const pw_layer_desc& d, int e0, int ne, size_t S, size_t S_all, bool apl) {
+  RangePlan r{};
+  r.e0 = e0;
+  r.ne = ne;
+  r.S = S;
+  if (ne <= 0) {
+    r.nsplit = 1;
+    r.kb_per_split = d.F / 128;
+    r.mtb = 1;
+    return r;
+  }
+  const int nkbF = d.F / 128;
+  const int expect = static_cast<int>((S + ne - 1) / ne);
+  r.path = pick_path(d, S, S_all, ne, apl, e0 > 0);
+  // The decode kernels split the down projection's K = F when too few
+  // (expert, 64-row block) units exist to fill the chip; deterministic in
+  // (desc, T, K). At four slot tiles a workgroup covers 256 rows, so fewer
+  // workgroups result, and that is kept: with that many slots per expert the
+  // fp32 partials of a split cost more than the fuller chip gains.
+  int nsplit = 1;
+  if (r.path == GemmPath::kDecode && S <= 4096) {
+    const size_t active = std::min<size_t>(ne, S);
+    const size_t units = active * (d.H / 64);
+    nsplit = static_cast<int>(std::max<size_t>(1, std::min<size_t>(8, 2048 / std::max<size_t>(units, 1))));
+  }
+  // likewise the streaming kernel with 32-slot tiles (bit-plane layers at
+  // decode sizes): 128-row down workgroups, two per CU
+  if (r.path == GemmPath::kStream && apl && expect <= 24 && S <= 4096) {
+    const size_t active = std::min<size_t>(ne, S);
+    const size_t units = active * (d.H / 128);
+    nsplit = static_cast<int>(std::max<size_t>(1, std::min<size_t>(8, 1024 / std::max<size_t>(units, 1))));
+  }
+  // and the tiled kernel in two when its down tiles (256 rows x 256 slots,
+  // one workgroup per CU) would run fewer than three rounds on the chip (the
+  // last, partly filled round then weighs less; three or four splits add
+  // more partial-sum traffic than they save)
+  if (r.path == GemmPath::kTiled) {
+    const size_t tiles = (S / 256 + static_cast<size_t>(ne)) * (d.H / 256);
+    nsplit = tiles < 3 * kCUs ? 2 : 1;
+  }
+  nsplit = std::min(nsplit, nkbF);
+  // a split holds whole quantization groups (G = 256, 512 span 2, 4 blocks)
+  const int bpg = d.G > 128 ? d.G / 128 : 1;
+  r.kb_per_split = ((nkbF + nsplit - 1) / nsplit + bpg - 1) / bpg * bpg;
+  r.nsplit = (nkbF + r.kb_per_split - 1) / r.kb_per_split;
+  // slot tiles per pass of the decode kernels: 1, 2 or 4 (with 4, a wave
+  // streams two 16-row weight tiles)
+  r.mtb = expect <= 12 ? 1 : expect <= 20 ? 2 : 4;
+  return r;
+}
+
+// 16-row weight tiles per wave of the decode kernels at one or two slot tiles
+// per pass (the bits are the same either way). Two halve the LDS operand
+// reads and the activation staging per weight byte, which is what waves on 8-
+// and 4-bit pages spend their issue slots on; waves on 16-bit pages wait for
+// memory, and there half as many, longer workgroups balance worse. So two
+// where at most an eighth of the pages are 16-bit, every expert expects a slot
+// and the workgroups still cover the chip. Measured, one / two (us a step): 8
+// experts of 4096 x 14336, 64 tokens, no 16-bit page 239 / 209, 12 % 267 / 251,
+// 25 % 300 / 291, 50 % 359 / 366; 33 tokens 216 / 204; one token (two experts)
+// 61 / 65; 64 experts of 2048 x 1408, 100 tokens, no 16-bit page 103 / 92;
+// 60 + 4 experts, 128 tokens, 25 % 164 / 165; 8 experts of 2048 x 4096, 16
+// tokens, no 16-bit page 47 / 42.
+inline int row_tiles(const pw_layer_desc& d, size_t n_16, size_t n_pages, const RangePlan& r) {
+  const size_t ne = static_cast<size_t>(r.ne);
+  return n_16 * 8 <= n_pages && r.S >= ne && ne * (d.F / 64) >= kCUs ? 2 : 1;
+}
+
+inline WsLayout ws_layout(const pw_layer_desc& d, int T, int K, bool apl, int n_shared) {
+  WsLayout w{};
+  const size_t S = static_cast<size_t>(T) * K;
+  const size_t S_sh = static_cast<size_t>(T) * n_shared;
+  w.r[0] = plan_range(d, 0, d.E - n_shared, S - S_sh, S, apl);
+  w.r[1] = plan_range(d, d.E - n_shared, n_shared, S_sh, S, apl);
+  auto al = [](size_t b) { return (b + 255) / 256 * 256; };
+  auto place = [&]() {
+    w.h_off = 0;
+    w.h_bytes = al(S * d.F * 2);
+    w.op_off = w.h_bytes;
+    w.op_bytes = al(static_cast<size_t>(std::max(w.r[0].nsplit, w.r[1].nsplit)) * S * d.H * 4);
+    w.total = w.h_bytes + w.op_bytes;
+  };
+  place();
+  // Narrow slot tiles split the down projection only where the partials leave
+  // the call within the static workspace of the allocation-free entry point.
+  if (w.total > kStaticScratchBytes) {
+    for (RangePlan& r : w.r) {
+      if (r.ne <= 0 || r.path != GemmPath::kTiled || (r.S + r.ne - 1) / r.ne >= 128) continue;
+      r.nsplit = 1;
+      r.kb_per_split = d.F / 128;
+    }
+    place();
+  }
+  return w;
+}
+
+// Whether a call forks work to the layer's own stream. A fork and join cost a
+// few microseconds in a graph and 10 to 40 issued call by call (two more
+// launches, two event records and two cross-stream waits), so:
+//   small layers (pages below kForkPages) never fork;
+//   shared experts fork above that: their few workgroups run beside the
+//     routed ones (60 + 4 experts of 2048 x 1408, 128 tokens: 164 us a step
+//     against 179 call by call, 157 against 184 in a graph; at 16 tokens 110
+//     either way and 104 against 114);
+//   the second routed chain forks only under stream capture, and where every
+//     expert expects a slot: in a graph it gains (8 experts of 4096 x 14336,
+//     64 tokens: 340 us against 351; 2048 x 7168: 111 against 114; tiny layer
+//     39 against 21), call by call it gains nothing (345 against 346) or loses
+//     (33 tokens on 4- and 8-bit pages 189 against 186, one token 112 against
+//     100, tiny layer 64 against 21).
+constexpr uint64_t kForkPages = uint64_t(256) << 20;
+
+inline bool may_fork(uint64_t pages) { return pages >= kForkPages; }
+
+// The shared experts' launches beside the routed ones.
+inline bool fork_shared(const WsLayout& w, uint64_t pages) {
+  return may_fork(pages) && w.r[0].ne > 0 && w.r[1].ne > 0;
+}
+
+// The routed range as two chains, under capture.
+inline bool fork_chains(const WsLayout& w, uint64_t pages) {
+  const RangePlan& r = w.r[0];
+  return may_fork(pages) && w.r[1].ne <= 0 && r.path == GemmPath::kDecode && r.ne >= 2 &&
+         r.S >= static_cast<size_t>(r.ne);
+}
+
+}  // namespace pw

@@ -1,13 +1,15 @@
-// CPU-only shim over the host-side protocol (pw_state.cpp) for the test suite:
-// the same allocator and requant / commit / reclaim state machine the library
-// runs, driven by a simulated event clock instead of HIP events. No device
-// memory is touched; a "launch" only records what would be enqueued.
+// CPU-only shim over the host-side protocol (pw_state.cpp) and the plan of a
+// paged GEMM call (pw_gemm_plan.hpp) for the test suite: the same allocator and
+// requant / commit / reclaim state machine the library runs, driven by a
+// simulated event clock instead of HIP events. No device memory is touched; a
+// "launch" only records what would be enqueued.
 #include <cstdint>
 #include <set>
 #include <string>
 #include <vector>
 
 #include "pw.h"
+#include "pw_gemm_plan.hpp"
 #include "pw_state.hpp"
 
 namespace {
@@ -211,6 +213,23 @@ void pwt_host_stats(void* hv, uint64_t* capacity, uint64_t* used) {
   Handle* h = static_cast<Handle*>(hv);
   *capacity = h->st.halloc.capacity();
   *used = h->st.halloc.used();
+}
+
+// The plan of one GEMM call: out[0] workspace bytes, then per range (routed,
+// shared) experts, slots, path, K splits, 128-blocks per split, slot tiles per
+// pass and row tiles per wave; out[15] and out[16]: whether the shared range
+// and the routed chains fork.
+void pwt_gemm_plan(const pw_layer_desc* d, int T, int K, int apl, int n_shared, uint64_t n_16, uint64_t n_pages,
+                   uint64_t page_bytes, int64_t* out) {
+  const pw::WsLayout w = pw::ws_layout(*d, T, K, apl != 0, n_shared);
+  *out++ = static_cast<int64_t>(w.total);
+  for (const pw::RangePlan& r : w.r) {
+    const int64_t v[7] = {r.ne, static_cast<int64_t>(r.S), static_cast<int64_t>(r.path), r.nsplit, r.kb_per_split,
+                          r.mtb, r.ne > 0 ? pw::row_tiles(*d, n_16, n_pages, r) : 0};
+    for (int64_t x : v) *out++ = x;
+  }
+  *out++ = pw::fork_shared(w, page_bytes) ? 1 : 0;
+  *out++ = pw::fork_chains(w, page_bytes) ? 1 : 0;
 }
 
 int pwt_all_present(void* hv) { return static_cast<Handle*>(hv)->st.all_present() ? 1 : 0; }

@@ -7,6 +7,7 @@
 #include <string>
 
 #include "pw.h"
+#include "pw_gemm_plan.hpp"
 
 namespace pw {
 
@@ -137,9 +138,8 @@ hipError_t launch_routing_stats(const uint16_t* rows, int act, int n_rows, int d
                                 const float* topk_w, const int32_t* offsets, const int32_t* sorted_slot, int S,
                                 int E, int K, double* norm2, double* stats, int accumulate, hipStream_t st);
 
-// Static device scratch of the allocation-free GEMM entry point: its
-// capacity, and its device address on `device` (looked up once per GPU).
-constexpr size_t kStaticScratchBytes = size_t(64) << 20;
+// Device address on `device` of the allocation-free GEMM entry point's static
+// scratch (kStaticScratchBytes; looked up once per GPU).
 hipError_t static_scratch(int device, void** ptr);
 
 // Error reporting of the C ABI (thread-local message, returned status).
