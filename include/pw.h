@@ -138,11 +138,17 @@ pw_status pw_layer_destroy(pw_layer* layer);
  * described by its table row). Place page (e, proj, rb) into a fresh pool
  * slot at `bits`: rows16_dev holds the page's R x K 16-bit values (act dtype,
  * row-major, device memory, read on `stream`). 16 -> copied; 8/4 ->
- * quantized on the GPU. The table entry is written on `stream` after the
- * data; later work on another stream must be ordered after `stream`.
+ * quantized on the GPU. The page and its table entry are valid together
+ * once `stream` passes the load; later work on another stream must be ordered
+ * after `stream`. (One launch writes both, the entry possibly before the last
+ * of the data: device code that looks at the table without being ordered
+ * after `stream` may see the entry early. The library's own readers cannot:
+ * the GEMM, the requantization and the copies refuse a page until the load
+ * call has returned, and run ordered after it.)
  *   bad block or bits: PW_EINVAL.  page present: PW_EBUSY.
- *   no free slot: PW_ENOMEM.  launch failed: PW_EHIP (the slot is released
- *   after `stream` drained).                                               */
+ *   no free slot: PW_ENOMEM.  launch failed, or an earlier HIP error of the
+ *   thread still pending: PW_EHIP (the entry is absent again, and the slot is
+ *   released, after `stream` drained).                                     */
 pw_status pw_layer_load_page(pw_layer* layer, int e, int proj, int rb, int bits,
                              const void* rows16_dev, void* stream);
 

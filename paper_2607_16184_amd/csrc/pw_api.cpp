@@ -183,6 +183,20 @@ pw_status write_entries(pw_layer* L, const std::vector<std::pair<size_t, pw_page
   return PW_OK;
 }
 
+// Takes back the entries of a load that failed after its launch: the launch
+// status also reports an error left pending by an earlier call of the thread,
+// so the entries may have been published, and their slots are about to be
+// released. Blocks until `st` is done with the pages. (Best effort: on a dead
+// device nothing reads the table either.)
+void unpublish(pw_layer* L, const std::vector<size_t>& idx, hipStream_t st) {
+  std::vector<std::pair<size_t, pw_page_entry>> w;
+  for (size_t i : idx) w.push_back({i, pw_page_entry{0, 0, 0, PW_PAGE_ABSENT, 0, 0}});
+  const std::string err = g_err;
+  (void)write_entries(L, w, st);
+  g_err = err;
+  drain(st);
+}
+
 // The layer's own stream and its fork/join events, created on the pool's
 // device (default priority; no implicit synchronization with the null
 // stream: the fork/join events order it).
@@ -314,9 +328,9 @@ pw_status pw_layer_load_page(pw_layer* L, int e, int proj, int rb, int bits, con
     ProfScope ps(L, PW_PH_REQUANT, st);
     he = pw::launch_qjob(j, st);
   }
-  if (he != hipSuccess) s = hip_fail(he, "page quantization launch");
-  if (s != PW_OK) {
-    drain(st);
+  if (he != hipSuccess) {
+    s = hip_fail(he, "page quantization launch");
+    unpublish(L, {L->st.index(e, proj, rb)}, st);
     L->st.abort_slot(ent, proj);
     return s;
   }
@@ -400,7 +414,7 @@ pw_status pw_layer_load_pages_apl(pw_layer* L, int n, const int* e, const int* p
   for (int i = 0; i < n; ++i) w.push_back({L->st.index(e[i], proj[i], rb[i]), ents[i]});
   pw_status s = write_entries(L, w, st);
   if (s != PW_OK) {
-    drain(st);
+    unpublish(L, std::vector<size_t>(seen.begin(), seen.end()), st);
     rollback(n);
     return s;
   }
