@@ -34,6 +34,20 @@ struct WsLayout {
   RangePlan r[2];      // routed, shared (ne = 0 without shared experts)
 };
 
+constexpr size_t kCUs = 256;
+
+// The tiled kernel's slot tiles: 256 slots, or 128 while an expert's expected
+// slots fit one of those with some room for the spread of the routing:
+// half-filled tiles would multiply and stage padding, while two 128-slot tiles
+// read the weights twice. Measured (256 / 128 slots, us a step): 8 experts of
+// 4096 x 14336 at 75 slots per expert 560 / 490, 105: 567 / 500, 140: 628 / 746,
+// 194: 672 / 788; 64 experts of 2048 x 1408 at 75: 291 / 247, 112: 309 / 275,
+// 187: 326 / 399.
+constexpr int kTileNarrow = 120;
+
+// Below this many slots per expert an expert's slots are about one tile.
+constexpr int kOneTileBelow = 128;
+
 // Which GEMM kernels serve a range, from its expected slots per expert
 // S / ne: up to 48, the decode kernels (weights streamed in registers, exact
 // code-domain arithmetic, up to four 16-slot tiles per pass); above, the
@@ -46,8 +60,6 @@ struct WsLayout {
 // CU a workgroup, the streaming kernel's smaller tiles spread their work. The
 // last two need 32/64-row staging inside one page, 128-row down blocks and
 // 32-bit activation row offsets (and the tiled kernel 256-row down blocks).
-constexpr size_t kCUs = 256;
-
 inline GemmPath pick_path(const pw_layer_desc& d, size_t S, size_t S_all, int ne, bool apl, bool shared) {
   const size_t expect = (S + ne - 1) / ne;
   const bool fits = S_all * d.F * 2 < (size_t(1) << 32) && S_all * d.H * 2 < (size_t(1) << 32);
@@ -94,13 +106,22 @@ inline RangePlan plan_range(const pw_layer_desc& d, int e0, int ne, size_t S, si
     const size_t units = active * (d.H / 128);
     nsplit = static_cast<int>(std::max<size_t>(1, std::min<size_t>(8, 1024 / std::max<size_t>(units, 1))));
   }
-  // and the tiled kernel in two when its down tiles (256 rows x 256 slots,
-  // one workgroup per CU) would run fewer than three rounds on the chip (the
-  // last, partly filled round then weighs less; three or four splits add
-  // more partial-sum traffic than they save)
+  // and the tiled kernel in two, by the tiles that its down projection has
+  // (one workgroup per CU). From 128 slots per expert: where they fill fewer
+  // than three rounds of the chip, so that the last, partly filled round weighs
+  // less. One split, or more than two, is at times better (8 experts of 4096 x
+  // 14336, one / two / three / four splits, us a step: 777 tokens 795 / 794 /
+  // 746 / 772, 1200 tokens 1020 / 1038 / 1049 / 1063). Below, about one tile per
+  // expert and 256 rows: where the halves still fit one round (one / two: 80
+  // slots each, 8 experts of 2048 x 4096 123 / 92, of 4096 x 7168 284 / 252, of
+  // 4096 x 14336 542 / 480, 32 of 1024 x 1024 64 / 62, 16 of 1024 x 2048 77 / 63; 126
+  // slots, 8 of 4096 x 14336 722 / 584, 32 of 1024 x 1024 82 / 75); with
+  // more tiles the partials cost more than the halves save (80 slots, 32 of
+  // 2048 x 512 75 / 86, 64 of 1024 x 512 63 / 74, of 2048 x 1408 222 / 243; 126
+  // slots 96 / 109, 77 / 91, 273 / 300).
   if (r.path == GemmPath::kTiled) {
-    const size_t tiles = (S / 256 + static_cast<size_t>(ne)) * (d.H / 256);
-    nsplit = tiles < 3 * kCUs ? 2 : 1;
+    const size_t rows = d.H / 256, one = static_cast<size_t>(ne) * rows;
+    nsplit = expect < kOneTileBelow ? (2 * one <= kCUs ? 2 : 1) : (S / 256 * rows + one < 3 * kCUs ? 2 : 1);
   }
   nsplit = std::min(nsplit, nkbF);
   // a split holds whole quantization groups (G = 256, 512 span 2, 4 blocks)
@@ -145,11 +166,12 @@ inline WsLayout ws_layout(const pw_layer_desc& d, int T, int K, bool apl, int n_
     w.total = w.h_bytes + w.op_bytes;
   };
   place();
-  // Narrow slot tiles split the down projection only where the partials leave
-  // the call within the static workspace of the allocation-free entry point.
+  // About one tile per expert: split the down projection only where the
+  // partials leave the call within the static workspace of the allocation-free
+  // entry point.
   if (w.total > kStaticScratchBytes) {
     for (RangePlan& r : w.r) {
-      if (r.ne <= 0 || r.path != GemmPath::kTiled || (r.S + r.ne - 1) / r.ne >= 128) continue;
+      if (r.ne <= 0 || r.path != GemmPath::kTiled || (r.S + r.ne - 1) / r.ne >= kOneTileBelow) continue;
       r.nsplit = 1;
       r.kb_per_split = d.F / 128;
     }

@@ -960,14 +960,6 @@ void tgemm_tm(const GemmArgs& a, bool gateup, hipStream_t st) {
     hipLaunchKernelGGL((k_tgemm<ACT, SDT, false, TM>), dim3(n, a.nsplit), dim3(64 * kWaves), 0, st, a, nblk);
 }
 
-// 256-slot tiles, or 128 while an expert's expected slots fit one of those
-// with some room for the spread of the routing: half-filled tiles would
-// multiply and stage padding, while two 128-slot tiles read the weights twice.
-// Measured (256 / 128 slots, us a step): 8 experts of 4096 x 14336 at 75 slots
-// per expert 560 / 490, 105: 567 / 500, 140: 628 / 746, 194: 672 / 788; 64
-// experts of 2048 x 1408 at 75: 291 / 247, 112: 309 / 275, 187: 326 / 399.
-constexpr int kTileNarrow = 120;
-
 template <int ACT, int SDT>
 void tgemm_go(const GemmArgs& a, bool gateup, hipStream_t st) {
   const int expect = (a.s_range + a.ne - 1) / a.ne;

@@ -1,0 +1,46 @@
+"""The plan of a paged GEMM call on the CPU: paths, workspace and forks as
+functions of the layer's shape and the batch."""
+import ctypes
+import os
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIBP = os.path.join(os.path.dirname(HERE), "paper_2607_16184_amd", "libpw_hosttest.so")
+
+DECODE, STREAM, TILED = range(3)
+
+
+class Desc(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("E", "H", "F", "R", "G", "act", "sdt")]
+
+
+class Range:
+    def __init__(self, v):
+        self.ne, self.S, self.path, self.nsplit, self.kb, self.mtb, self.rt = v
+
+
+class Plan:
+    def __init__(self, E, K, H, F, T, n_shared=0, apl=False, n_16=0, n_pages=1, pages=0):
+        if not os.path.exists(LIBP):
+            from paper_2607_16184_amd import build
+            build.build_hosttest()
+        lib = ctypes.CDLL(LIBP)
+        lib.pwt_gemm_plan.restype = None
+        lib.pwt_gemm_plan.argtypes = ([ctypes.POINTER(Desc)] + [ctypes.c_int] * 4 + [ctypes.c_uint64] * 3
+                                      + [ctypes.POINTER(ctypes.c_int64)])
+        out = (ctypes.c_int64 * 17)()
+        lib.pwt_gemm_plan(ctypes.byref(Desc(E, H, F, 64, 128, 1, 1)), T, K, int(apl), n_shared, n_16, n_pages, pages, out)
+        self.total = out[0]
+        self.routed, self.shared = Range(out[1:8]), Range(out[8:15])
+        self.fork_shared, self.fork_chains = bool(out[15]), bool(out[16])
+
+
+@pytest.mark.parametrize("E,K,H,F,slots,nsplit", [
+    (8, 2, 2048, 4096, 80, 2), (8, 2, 4096, 7168, 80, 2), (32, 4, 1024, 1024, 80, 2), (16, 4, 1024, 2048, 80, 2),
+    (64, 6, 1024, 768, 80, 1), (64, 6, 2048, 1408, 50, 1), (64, 6, 2048, 1408, 118, 1),     # more than half a round
+    (64, 6, 1024, 512, 126, 1), (8, 2, 4096, 7168, 124, 2), (8, 2, 4096, 14336, 194, 2),     # 256-slot tiles
+])
+def test_down_splits_of_the_tiled_kernel(E, K, H, F, slots, nsplit):
+    r = Plan(E, K, H, F, slots * E // K).routed
+    assert r.path == TILED and r.nsplit == nsplit
