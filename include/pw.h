@@ -225,7 +225,9 @@ pw_status pw_route_topk_shared(const float* logits, int T, int E, int K, int ren
                                const float* shared_gate, int32_t* topk_ids, float* topk_w,
                                int32_t* offsets, int32_t* sorted_slot, int32_t* slot_pos, void* stream);
 
-/* Workspace bytes pw_moe_paged_gemm needs for T tokens with top-K. */
+/* Workspace bytes pw_moe_paged_gemm uses for T tokens with top-K. (Between 49
+ * and 127 slots per expert the call also runs with less: one copy of the down
+ * projection's partials in the place of two, T K (2 F + 4 H) bytes in all.) */
 pw_status pw_workspace_bytes(const pw_layer* layer, int T, int K, size_t* gemm_ws);
 
 /* Paged expert forward and combine (Sec. 3.3): for each routed slot (t,k)
@@ -235,7 +237,8 @@ pw_status pw_workspace_bytes(const pw_layer* layer, int T, int K, size_t* gemm_w
  * before the down projection.
  *   x [T,H] act device; y [T,H] act, or fp32 if out_fp32 != 0.
  *   topk_w, offsets, sorted_slot, slot_pos: as produced by pw_route_topk.
- *   ws: device workspace of at least pw_workspace_bytes bytes.
+ *   ws: device workspace of at least pw_workspace_bytes bytes (PW_ENOMEM
+ *   below the need).
  * Requires every page of the layer to be present (PW_ESTATE otherwise).
  * Sizes: T*K < 2^31, and T*K*max(F, H)*2 < 2^32 (32-bit row offsets in the
  * kernels; PW_EUNSUPPORTED otherwise: split the batch).
@@ -260,7 +263,7 @@ pw_status pw_moe_paged_gemm(const pw_layer* layer, const void* x, int T, int K,
  * GPU shares its array and overwrites what the last call left there (no part
  * of it needs to start zeroed): calls that overlap on one GPU (two streams,
  * two threads) race, and the caller serializes them.
- *   workspace need (pw_workspace_bytes) above 64 MiB, e.g. prefill batches
+ *   workspace need (as pw_moe_paged_gemm's) above 64 MiB, e.g. prefill batches
  *   of large layers: PW_ENOMEM (use pw_moe_paged_gemm).  Other errors: as
  *   pw_moe_paged_gemm.                                                     */
 pw_status pw_moe_paged_gemm_noalloc(const pw_layer* layer, const void* x, int T, int K,

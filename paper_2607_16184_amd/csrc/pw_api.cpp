@@ -530,7 +530,7 @@ pw_status pw_moe_paged_gemm(const pw_layer* Lc, const void* x, int T, int K, con
     if (S * L->st.desc.F * 2 >= lim || S * L->st.desc.H * 2 >= lim)
       return fail(PW_EUNSUPPORTED, "T*K*max(F,H)*2 must stay below 2^32 (split the batch)");
   }
-  const pw::WsLayout wl = pw::ws_layout(L->st.desc, T, K, L->st.n_apl > 0, L->n_shared);
+  const pw::WsLayout wl = pw::ws_layout(L->st.desc, T, K, L->st.n_apl > 0, L->n_shared, ws_bytes);
   if (L->st.n_apl > 0) {
     const pw_layer_desc& dd = L->st.desc;
     const size_t S = static_cast<size_t>(T) * K;
@@ -662,7 +662,7 @@ pw_status pw_moe_paged_gemm_noalloc(const pw_layer* L, const void* x, int T, int
   if (L->n_shared > 0 && K <= L->n_shared) return fail(PW_EINVAL, "K must exceed the shared experts");
   if (T == 0) return PW_OK;
   if (static_cast<int64_t>(T) * K >= (int64_t(1) << 31)) return fail(PW_EINVAL, "T*K too large");
-  const size_t need = pw::ws_layout(L->st.desc, T, K, L->st.n_apl > 0, L->n_shared).total;
+  const size_t need = pw::ws_layout(L->st.desc, T, K, L->st.n_apl > 0, L->n_shared, pw::kStaticScratchBytes).total;
   if (need > pw::kStaticScratchBytes)
     return fail(PW_ENOMEM, "the call needs " + std::to_string(need) + " bytes of workspace, more than the " +
                                std::to_string(pw::kStaticScratchBytes) +

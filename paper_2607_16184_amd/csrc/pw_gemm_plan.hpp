@@ -151,7 +151,12 @@ inline int row_tiles(const pw_layer_desc& d, size_t n_16, size_t n_pages, const 
   return n_16 * 8 <= n_pages && r.S >= ne && ne * (d.F / 64) >= kCUs ? 2 : 1;
 }
 
-inline WsLayout ws_layout(const pw_layer_desc& d, int T, int K, bool apl, int n_shared) {
+// The workspace of a call that has `ws_bytes` of it. A tiled range below
+// kOneTileBelow needs one copy of the down partials, as it did when the
+// streaming kernel, which does not split, served it: where two do not fit, it
+// runs unsplit. The call is refused where `total` is still above ws_bytes.
+// Without a limit, `total` is what the plan can use (pw_workspace_bytes).
+inline WsLayout ws_layout(const pw_layer_desc& d, int T, int K, bool apl, int n_shared, size_t ws_bytes = SIZE_MAX) {
   WsLayout w{};
   const size_t S = static_cast<size_t>(T) * K;
   const size_t S_sh = static_cast<size_t>(T) * n_shared;
@@ -166,10 +171,7 @@ inline WsLayout ws_layout(const pw_layer_desc& d, int T, int K, bool apl, int n_
     w.total = w.h_bytes + w.op_bytes;
   };
   place();
-  // About one tile per expert: split the down projection only where the
-  // partials leave the call within the static workspace of the allocation-free
-  // entry point.
-  if (w.total > kStaticScratchBytes) {
+  if (w.total > ws_bytes) {
     for (RangePlan& r : w.r) {
       if (r.ne <= 0 || r.path != GemmPath::kTiled || (r.S + r.ne - 1) / r.ne >= kOneTileBelow) continue;
       r.nsplit = 1;

@@ -215,13 +215,13 @@ void pwt_host_stats(void* hv, uint64_t* capacity, uint64_t* used) {
   *used = h->st.halloc.used();
 }
 
-// The plan of one GEMM call: out[0] workspace bytes, then per range (routed,
+// The plan of one GEMM call that has ws_bytes of workspace: out[0] bytes needed, then per range (routed,
 // shared) experts, slots, path, K splits, 128-blocks per split, slot tiles per
 // pass and row tiles per wave; out[15] and out[16]: whether the shared range
 // and the routed chains fork.
 void pwt_gemm_plan(const pw_layer_desc* d, int T, int K, int apl, int n_shared, uint64_t n_16, uint64_t n_pages,
-                   uint64_t page_bytes, int64_t* out) {
-  const pw::WsLayout w = pw::ws_layout(*d, T, K, apl != 0, n_shared);
+                   uint64_t page_bytes, uint64_t ws_bytes, int64_t* out) {
+  const pw::WsLayout w = pw::ws_layout(*d, T, K, apl != 0, n_shared, ws_bytes);
   *out++ = static_cast<int64_t>(w.total);
   for (const pw::RangePlan& r : w.r) {
     const int64_t v[7] = {r.ne, static_cast<int64_t>(r.S), static_cast<int64_t>(r.path), r.nsplit, r.kb_per_split,

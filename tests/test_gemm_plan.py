@@ -9,6 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIBP = os.path.join(os.path.dirname(HERE), "paper_2607_16184_amd", "libpw_hosttest.so")
 
 DECODE, STREAM, TILED = range(3)
+NO_LIMIT = (1 << 64) - 1
 
 
 class Desc(ctypes.Structure):
@@ -21,16 +22,17 @@ class Range:
 
 
 class Plan:
-    def __init__(self, E, K, H, F, T, n_shared=0, apl=False, n_16=0, n_pages=1, pages=0):
+    def __init__(self, E, K, H, F, T, n_shared=0, apl=False, n_16=0, n_pages=1, pages=0, ws=NO_LIMIT):
         if not os.path.exists(LIBP):
             from paper_2607_16184_amd import build
             build.build_hosttest()
         lib = ctypes.CDLL(LIBP)
         lib.pwt_gemm_plan.restype = None
-        lib.pwt_gemm_plan.argtypes = ([ctypes.POINTER(Desc)] + [ctypes.c_int] * 4 + [ctypes.c_uint64] * 3
+        lib.pwt_gemm_plan.argtypes = ([ctypes.POINTER(Desc)] + [ctypes.c_int] * 4 + [ctypes.c_uint64] * 4
                                       + [ctypes.POINTER(ctypes.c_int64)])
         out = (ctypes.c_int64 * 17)()
-        lib.pwt_gemm_plan(ctypes.byref(Desc(E, H, F, 64, 128, 1, 1)), T, K, int(apl), n_shared, n_16, n_pages, pages, out)
+        lib.pwt_gemm_plan(ctypes.byref(Desc(E, H, F, 64, 128, 1, 1)), T, K, int(apl), n_shared, n_16, n_pages, pages,
+                          ws, out)
         self.total = out[0]
         self.routed, self.shared = Range(out[1:8]), Range(out[8:15])
         self.fork_shared, self.fork_chains = bool(out[15]), bool(out[16])
@@ -44,3 +46,30 @@ class Plan:
 def test_down_splits_of_the_tiled_kernel(E, K, H, F, slots, nsplit):
     r = Plan(E, K, H, F, slots * E // K).routed
     assert r.path == TILED and r.nsplit == nsplit
+
+
+def _one_copy(T, K, H, F):
+    return T * K * (2 * F + 4 * H)
+
+
+@pytest.mark.parametrize("E,K,H,F", [(64, 6, 2048, 1408), (32, 1, 4096, 128), (8, 2, 4096, 28672), (16, 4, 1024, 2048)])
+def test_workspace_between_49_and_127_slots(E, K, H, F):
+    """Every call of the range runs with one copy of the partials, so a
+    workspace sized for more tokens always serves fewer; with room for two,
+    the plan's split is used, whatever the static scratch holds."""
+    lo, hi = -(-49 * E // K), 127 * E // K
+    for T in range(lo, hi + 1, max(1, (hi - lo) // 97)):
+        need = _one_copy(T, K, H, F)
+        full = Plan(E, K, H, F, T)
+        least = Plan(E, K, H, F, T, ws=need)
+        assert least.total <= need + 512 and least.routed.nsplit == 1, T    # two 256-byte roundings
+        assert Plan(E, K, H, F, T, ws=full.total).routed.nsplit == full.routed.nsplit
+        if T + 1 <= hi:
+            assert full.total <= Plan(E, K, H, F, T + 1).total, T
+
+
+def test_workspace_from_128_slots_is_not_cut():
+    """The two-copy need of larger batches stands: less is refused."""
+    full = Plan(8, 2, 4096, 14336, 777)
+    assert full.routed.path == TILED and full.routed.nsplit == 2
+    assert Plan(8, 2, 4096, 14336, 777, ws=full.total - 1).total == full.total
