@@ -51,15 +51,24 @@ constexpr int kOneTileBelow = 128;
 // Which GEMM kernels serve a range, from its expected slots per expert
 // S / ne: up to 48, the decode kernels (weights streamed in registers, exact
 // code-domain arithmetic, up to four 16-slot tiles per pass); above, the
-// LDS-tiled kernel (256 weight rows x 128 or 256 slots; at 55, 75 and 105
-// slots per expert of 4096 x 14336 it takes 441, 490 and 500 us a step, the
-// streaming kernel 493, 641 and 664 us). The streaming kernel (64-slot tiles)
-// serves bit-plane layers and shapes whose down projection is not a multiple
-// of 256 rows. The shared experts of a decode-sized batch are a few experts with a
-// few hundred slots each: where the tiled kernel's tiles would not give every
-// CU a workgroup, the streaming kernel's smaller tiles spread their work. The
-// last two need 32/64-row staging inside one page, 128-row down blocks and
-// 32-bit activation row offsets (and the tiled kernel 256-row down blocks).
+// LDS-tiled kernel (256 weight rows x 128 or 256 slots) or the streaming one
+// (64-slot tiles). The streaming kernel serves
+//   bit-plane layers, and shapes whose down projection is not a multiple of
+//   256 rows;
+//   ranges below 128 slots per expert whose gate/up has fewer tiles than the
+//   chip has CUs: a tile takes its time however few there are, and smaller
+//   tiles spread the work (streaming / tiled, us a step, one tile per expert
+//   and 128 rows of F: 4 experts of 1024 x 2048 at 80 slots 46 / 55, of 4096 x
+//   4096 107 / 122, 8 of 1024 x 2048 54 / 58 and at 126 slots 61 / 76; with the
+//   chip filled, 8 of 2048 x 4096 at 80 129 / 92, 16 of 1024 x 2048 82 / 63, 8 of
+//   4096 x 14336 614 / 480). From 16 experts on half the chip is enough at 65
+//   to 120 slots, where an expert takes two 64-slot tiles but one of 128: 16
+//   of 2048 x 1024 at 80 81 / 74, 32 of 1024 x 512 62 / 55;
+//   shared experts whose tiles do not fill the chip (a few experts with a few
+//   hundred slots each in a decode-sized batch).
+// The last two kernels need 32/64-row staging inside one page, 128-row down
+// blocks and 32-bit activation row offsets (and the tiled kernel 256-row down
+// blocks).
 inline GemmPath pick_path(const pw_layer_desc& d, size_t S, size_t S_all, int ne, bool apl, bool shared) {
   const size_t expect = (S + ne - 1) / ne;
   const bool fits = S_all * d.F * 2 < (size_t(1) << 32) && S_all * d.H * 2 < (size_t(1) << 32);
@@ -67,8 +76,10 @@ inline GemmPath pick_path(const pw_layer_desc& d, size_t S, size_t S_all, int ne
   // nested bit-plane pages are read by the streaming kernel only
   if (apl) return GemmPath::kStream;
   if (expect > 48 && tiles && d.H % 256 == 0) {
-    const size_t tiled_wgs = static_cast<size_t>(ne) * ((expect + 255) / 256) * (d.F / 128);
-    return shared && tiled_wgs < kCUs ? GemmPath::kStream : GemmPath::kTiled;
+    const size_t blocks = static_cast<size_t>(ne) * (d.F / 128);
+    if (shared) return blocks * ((expect + 255) / 256) < kCUs ? GemmPath::kStream : GemmPath::kTiled;
+    const bool half = ne >= 16 && 2 * blocks >= kCUs && expect > 64 && expect <= kTileNarrow;
+    return expect >= kOneTileBelow || blocks >= kCUs || half ? GemmPath::kTiled : GemmPath::kStream;
   }
   if (expect > 48 && tiles && d.H % 128 == 0) return GemmPath::kStream;
   return GemmPath::kDecode;

@@ -34,6 +34,29 @@ def gpu_layer(cfg, w16, bits, order, slack=0.0):
     return L
 
 
+def gpu_random_layer(cfg, mix=(16, 8, 4), slack=0.0):
+    """A layer whose weights, N(0, 0.02), are drawn on the GPU page by page (for
+    layers too large to draw on the host); bitwidths cycle through ``mix`` along
+    each expert's row blocks, starting one further for every expert."""
+    import torch
+    from paper_2607_16184_amd import pw
+    from paper_2607_16184_amd.layer import PagedLayer
+    bits = [np.array([[mix[(e + p + rb) % len(mix)] for rb in range(cfg.nrb(p))] for e in range(cfg.E)], np.int32)
+            for p in range(3)]
+    L = PagedLayer(cfg, PagedLayer.pool_bytes_for(cfg, bits, slack))
+    g = torch.Generator(device="cuda").manual_seed(11)
+    st = torch.cuda.current_stream().cuda_stream
+    dt = torch.bfloat16 if cfg.act == synth.BF16 else torch.float16
+    for e in range(cfg.E):
+        for p in range(3):
+            rows, cols = (cfg.H, cfg.F) if p == 2 else (cfg.F, cfg.H)
+            w = (torch.randn((rows, cols), generator=g, device="cuda") * 0.02).to(dt)
+            for rb in range(cfg.nrb(p)):
+                pw.pw_layer_load_page(L.handle, e, p, rb, int(bits[p][e, rb]), w[rb * cfg.R].data_ptr(), st)
+            torch.cuda.current_stream().synchronize()
+    return L
+
+
 def rel_err(y, r):
     """max |y - r| / max |r| over the tensor."""
     y = np.asarray(y, np.float64)

@@ -38,6 +38,22 @@ class Plan:
         self.fork_shared, self.fork_chains = bool(out[15]), bool(out[16])
 
 
+@pytest.mark.parametrize("E,K,H,F,slots,path", [
+    # gate/up tiles below the 256 CUs: the streaming kernel up to 127 slots ...
+    (4, 1, 512, 512, 50, STREAM), (4, 1, 1024, 2048, 126, STREAM), (4, 2, 4096, 4096, 80, STREAM),
+    (8, 2, 256, 512, 75, STREAM), (8, 2, 1024, 2048, 100, STREAM), (16, 2, 1024, 1024, 50, STREAM),
+    (16, 2, 1024, 1024, 124, STREAM), (8, 2, 1024, 2048, 128, TILED), (4, 1, 512, 512, 128, TILED),
+    # ... but for 16 or more experts of 65 to 120 slots, and half the CUs
+    (16, 2, 1024, 1024, 65, TILED), (32, 4, 1024, 512, 120, TILED), (32, 4, 1024, 384, 80, STREAM),
+    # a tile for every CU
+    (8, 2, 2048, 4096, 50, TILED), (8, 2, 4096, 14336, 75, TILED), (64, 6, 1024, 512, 124, TILED),
+    # no 256-row down blocks
+    (8, 2, 384, 4096, 80, STREAM), (8, 2, 384, 4096, 300, STREAM), (8, 2, 256, 512, 48, DECODE),
+])
+def test_path_of_the_routed_experts(E, K, H, F, slots, path):
+    assert Plan(E, K, H, F, slots * E // K).routed.path == path
+
+
 @pytest.mark.parametrize("E,K,H,F,slots,nsplit", [
     (8, 2, 2048, 4096, 80, 2), (8, 2, 4096, 7168, 80, 2), (32, 4, 1024, 1024, 80, 2), (16, 4, 1024, 2048, 80, 2),
     (64, 6, 1024, 768, 80, 1), (64, 6, 2048, 1408, 50, 1), (64, 6, 2048, 1408, 118, 1),     # more than half a round
@@ -62,6 +78,8 @@ def test_workspace_between_49_and_127_slots(E, K, H, F):
         need = _one_copy(T, K, H, F)
         full = Plan(E, K, H, F, T)
         least = Plan(E, K, H, F, T, ws=need)
+        if full.routed.path != TILED:
+            continue
         assert least.total <= need + 512 and least.routed.nsplit == 1, T    # two 256-byte roundings
         assert Plan(E, K, H, F, T, ws=full.total).routed.nsplit == full.routed.nsplit
         if T + 1 <= hi:

@@ -1,11 +1,13 @@
-"""Edges of the tiled paged GEMM: expert slot counts around the tile widths,
-every group layout (scale/zero groups of 64, 128, 256 values in 4- and 8-bit
-units), short reductions and mixed page formats, against the CPU oracle.
+"""Edges of the tiled and the streaming paged GEMM: expert slot counts around
+the tile widths, every group layout (scale/zero groups of 64, 128, 256 values in
+4- and 8-bit units), short reductions and mixed page formats, against the CPU
+oracle. (F = 8192 gives 4 experts a gate/up tile for every CU, which the tiled
+kernel needs below 128 slots per expert.)
 
-The kernel multiplies quantized weights rounded to the activation dtype
-(w_round) and rounds the SwiGLU output there too; what is left between the
-two is the order of fp32 sums over K <= 640 products, far below the 1e-3
-allowed (the bound the other fp32 parity tests use). The decode kernels'
+The kernels multiply quantized weights rounded to the activation dtype
+(w_round) and round the SwiGLU output there too; what is left between the
+two is the order of fp32 sums over K <= 8192 products (about sqrt(K) 2^-24,
+5e-6), far below the 1e-3 allowed (the bound the other fp32 parity tests use). The decode kernels'
 two-row-tile form (layers with few 16-bit pages) keeps weights exact, so it
 is held to the same bound against the plain oracle.
 """
@@ -15,7 +17,7 @@ import numpy as np
 import pytest
 
 import oracle
-from helpers import gpu_layer, oracle_layer, rel_err, say, to_dev, to_dev16
+from helpers import gpu_layer, gpu_random_layer, oracle_layer, rel_err, say, to_dev, to_dev16
 from paper_2607_16184_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -24,8 +26,11 @@ F16, BF16 = synth.F16, synth.BF16
 
 
 @pytest.mark.parametrize("counts,H,F,R,G,act,sdt", [
-    ((1, 127, 128, 129), 256, 256, 64, 64, F16, F16),       # 128-slot tiles, one slot, full, one over
-    ((63, 0, 250, 65), 256, 384, 64, 128, BF16, BF16),      # an empty expert, two tiles
+    ((1, 127, 128, 129), 256, 256, 64, 64, F16, F16),       # streaming, 64-slot tiles: one slot, ragged, full, one over
+    ((63, 0, 250, 65), 256, 384, 64, 128, BF16, BF16),      # streaming: an empty expert, four tiles
+    ((1, 127, 128, 129), 256, 8192, 64, 64, F16, F16),      # 128-slot tiles, one slot, full, one over
+    ((63, 0, 250, 65), 256, 8192, 64, 128, BF16, BF16),     # an empty expert, two tiles
+    ((64, 49, 17, 90), 512, 8192, 128, 256, F16, BF16),     # groups over two 128-blocks
     ((255, 256, 257, 0), 512, 256, 128, 256, BF16, F16),    # 256-slot tiles
     ((500, 16, 17, 15), 256, 640, 64, 64, BF16, BF16),      # skew: idle waves in most tiles
     ((300, 129, 240, 1), 768, 128, 128, 128, F16, BF16),    # K = 128: one block per row of the down pages
@@ -99,6 +104,40 @@ def test_narrow_tiles_keep_within_static_workspace():
                                  sp.data_ptr(), y.data_ptr(), 1, torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     assert torch.equal(y, want)
+    L.close()
+
+
+def test_split_follows_the_workspace():
+    """120 slots per expert over 128 experts: the plan splits the down projection
+    in two, which takes more than the static 64 MiB. With a workspace for one
+    copy of the partials, and through the allocation-free entry point, the call
+    runs unsplit with the same bits; with one byte less it is refused. The
+    split sums the same products in another order (F = 1280: relative 1e-5)."""
+    import torch
+    from paper_2607_16184_amd import pw
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], E=128, K=1, H=256, F=1280, T=15360, act=BF16, sdt=BF16)
+    say("split by the workspace, 128 experts")
+    L = gpu_random_layer(cfg)
+    one = cfg.T * (cfg.F * 2 + cfg.H * 4)
+    full = pw.pw_workspace_bytes(L.handle, cfg.T, 1)
+    assert one <= 64 << 20 < full == one + cfg.T * cfg.H * 4
+    x = to_dev16(synth.activations(cfg))
+    routing = L.route(to_dev(synth.logits(cfg)), 1)
+    split = L.forward(x, routing, out_fp32=True)
+    _, w, off, ss, sp = routing
+    ptrs = (w.data_ptr(), off.data_ptr(), ss.data_ptr(), sp.data_ptr())
+    st = torch.cuda.current_stream().cuda_stream
+    ws = torch.empty(one + 256, dtype=torch.uint8, device="cuda")
+    base = (ws.data_ptr() + 255) // 256 * 256
+    small, static = torch.full_like(split, float("nan")), torch.full_like(split, float("nan"))
+    pw.pw_moe_paged_gemm(L.handle, x.data_ptr(), cfg.T, 1, *ptrs, small.data_ptr(), 1, base, one, st)
+    pw.pw_moe_paged_gemm_noalloc(L.handle, x.data_ptr(), cfg.T, 1, *ptrs, static.data_ptr(), 1, st)
+    with pytest.raises(pw.PWError) as ei:
+        pw.pw_moe_paged_gemm(L.handle, x.data_ptr(), cfg.T, 1, *ptrs, small.data_ptr(), 1, base, one - 1, st)
+    assert ei.value.status == pw.PW_ENOMEM
+    torch.cuda.synchronize()
+    assert torch.equal(small, static)
+    assert rel_err(small.cpu().numpy(), split.cpu().numpy()) <= 1e-5
     L.close()
 
 
