@@ -530,7 +530,9 @@ pw_status pw_moe_paged_gemm(const pw_layer* Lc, const void* x, int T, int K, con
     if (S * L->st.desc.F * 2 >= lim || S * L->st.desc.H * 2 >= lim)
       return fail(PW_EUNSUPPORTED, "T*K*max(F,H)*2 must stay below 2^32 (split the batch)");
   }
-  const pw::WsLayout wl = pw::ws_layout(L->st.desc, T, K, L->st.n_apl > 0, L->n_shared, ws_bytes);
+  pw::WsLayout wl = pw::ws_layout(L->st.desc, T, K, L->st.n_apl > 0, L->n_shared, ws_bytes);
+  for (pw::RangePlan& r : wl.r)
+    if (r.ne > 0) r.rt = pw::row_tiles(L->st.desc, L->st.n_16, L->st.n_pages, r);
   if (L->st.n_apl > 0) {
     const pw_layer_desc& dd = L->st.desc;
     const size_t S = static_cast<size_t>(T) * K;
@@ -608,7 +610,7 @@ pw_status pw_moe_paged_gemm(const pw_layer* Lc, const void* x, int T, int K, con
     a.nsplit = r.nsplit;
     a.kb_per_split = r.kb_per_split;
     a.mtb = r.mtb;
-    a.rt = pw::row_tiles(L->st.desc, L->st.n_16, L->st.n_pages, r);
+    a.rt = r.rt;
   };
   const char* what = nullptr;
   {

@@ -27,6 +27,7 @@ struct RangePlan {
   size_t S;            // slots routed to them
   GemmPath path;
   int nsplit, kb_per_split, mtb;
+  int rt;              // row tiles per wave of the decode kernels (row_tiles)
 };
 
 struct WsLayout {
@@ -142,24 +143,32 @@ inline RangePlan plan_range(const pw_layer_desc& d, int e0, int ne, size_t S, si
   // slot tiles per pass of the decode kernels: 1, 2 or 4 (with 4, a wave
   // streams two 16-row weight tiles)
   r.mtb = expect <= 12 ? 1 : expect <= 20 ? 2 : 4;
+  r.rt = 1;
   return r;
 }
 
 // 16-row weight tiles per wave of the decode kernels at one or two slot tiles
-// per pass (the bits are the same either way). Two halve the LDS operand
-// reads and the activation staging per weight byte, which is what waves on 8-
-// and 4-bit pages spend their issue slots on; waves on 16-bit pages wait for
-// memory, and there half as many, longer workgroups balance worse. So two
-// where at most an eighth of the pages are 16-bit, every expert expects a slot
-// and the workgroups still cover the chip. Measured, one / two (us a step): 8
-// experts of 4096 x 14336, 64 tokens, no 16-bit page 239 / 209, 12 % 267 / 251,
-// 25 % 300 / 291, 50 % 359 / 366; 33 tokens 216 / 204; one token (two experts)
-// 61 / 65; 64 experts of 2048 x 1408, 100 tokens, no 16-bit page 103 / 92;
-// 60 + 4 experts, 128 tokens, 25 % 164 / 165; 8 experts of 2048 x 4096, 16
-// tokens, no 16-bit page 47 / 42.
+// per pass (the bits are the same either way), for a whole expert range. Two
+// halve the LDS operand reads and the activation staging per weight byte, which
+// is what waves on 8- and 4-bit pages spend their issue slots on; waves on
+// 16-bit pages wait for memory, and there half as many, longer workgroups
+// balance worse, the more so the longer their rows. So two where the
+// workgroups still cover the chip and
+//   at two slot tiles, at most an eighth of the pages are 16-bit (one / two, us
+//   a step: 8 experts of 4096 x 14336, 64 tokens, no 16-bit page 230 / 202, 12 %
+//   256 / 244, 25 % 300 / 291, 50 % 359 / 366; of 4096 x 4096, 12 % 94.5 / 94.4);
+//   at one, the share of 16-bit pages times H is at most 96 (8 experts of 4096 x
+//   14336, 33 tokens, none 195 / 189, 6 % 214 / 217, 12 % 231 / 233; of 4096 x 4096,
+//   16 tokens, none 67.5 / 67.6, 3 % 71 / 75, 12 % 81 / 87; 64 of 2048 x 1408, 33
+//   tokens, none 90 / 86, 3 % 93.5 / 90.4, 6 % 95.5 / 97.1; 64 of 1024 x 1408, 6 %
+//   65 / 61, 12 % 67 / 64), every expert expects two slots or more (4 tokens: 8 of
+//   4096 x 4096 52 / 56, one token of 4096 x 14336 61 / 65), and ten or fewer, so
+//   that few experts take a second pass (8 of 4096 x 4096, 48 tokens 89 / 94).
 inline int row_tiles(const pw_layer_desc& d, size_t n_16, size_t n_pages, const RangePlan& r) {
   const size_t ne = static_cast<size_t>(r.ne);
-  return n_16 * 8 <= n_pages && r.S >= ne && ne * (d.F / 64) >= kCUs ? 2 : 1;
+  if (ne * (d.F / 64) < kCUs) return 1;
+  if (r.mtb == 2) return n_16 * 8 <= n_pages ? 2 : 1;
+  return n_16 * d.H <= 96 * n_pages && r.S >= 2 * ne && r.S <= 10 * ne ? 2 : 1;
 }
 
 // The workspace of a call that has `ws_bytes` of it. A tiled range below

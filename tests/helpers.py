@@ -34,16 +34,17 @@ def gpu_layer(cfg, w16, bits, order, slack=0.0):
     return L
 
 
-def gpu_random_layer(cfg, mix=(16, 8, 4), slack=0.0):
-    """A layer whose weights, N(0, 0.02), are drawn on the GPU page by page (for
-    layers too large to draw on the host); bitwidths cycle through ``mix`` along
-    each expert's row blocks, starting one further for every expert."""
+def gpu_random_layer(cfg, mix=(16, 8, 4), bits=None):
+    """A layer whose weights, N(0, 0.02), are drawn on the GPU expert by expert
+    (for layers too large to draw on the host); without ``bits``, bitwidths cycle
+    through ``mix`` along each expert's row blocks, starting one further for
+    every expert."""
     import torch
     from paper_2607_16184_amd import pw
     from paper_2607_16184_amd.layer import PagedLayer
-    bits = [np.array([[mix[(e + p + rb) % len(mix)] for rb in range(cfg.nrb(p))] for e in range(cfg.E)], np.int32)
-            for p in range(3)]
-    L = PagedLayer(cfg, PagedLayer.pool_bytes_for(cfg, bits, slack))
+    bits = bits or [np.array([[mix[(e + p + rb) % len(mix)] for rb in range(cfg.nrb(p))] for e in range(cfg.E)], np.int32)
+                    for p in range(3)]
+    L = PagedLayer(cfg, PagedLayer.pool_bytes_for(cfg, bits))
     g = torch.Generator(device="cuda").manual_seed(11)
     st = torch.cuda.current_stream().cuda_stream
     dt = torch.bfloat16 if cfg.act == synth.BF16 else torch.float16

@@ -64,6 +64,19 @@ def test_down_splits_of_the_tiled_kernel(E, K, H, F, slots, nsplit):
     assert r.path == TILED and r.nsplit == nsplit
 
 
+@pytest.mark.parametrize("E,K,H,F,T,share16,rt", [
+    (8, 2, 4096, 14336, 33, 0.0, 2), (8, 2, 4096, 14336, 33, 0.06, 1), (8, 2, 4096, 4096, 16, 0.1, 1),
+    (8, 2, 4096, 4096, 4, 0.0, 1), (8, 2, 4096, 4096, 48, 0.0, 1), (64, 6, 2048, 1408, 33, 0.03, 2),
+    (64, 6, 2048, 1408, 33, 0.06, 1), (64, 6, 1024, 1408, 33, 0.09, 2), (64, 6, 1024, 1408, 33, 0.12, 1),
+    (8, 2, 4096, 14336, 64, 0.0, 2), (8, 2, 4096, 14336, 64, 0.12, 2), (8, 2, 4096, 14336, 64, 0.13, 1),   # two slot tiles
+    (8, 2, 256, 512, 16, 0.0, 1),                                                      # too few workgroups
+])
+def test_row_tiles_of_the_decode_kernels(E, K, H, F, T, share16, rt):
+    n = E * (2 * F + H) // 64
+    r = Plan(E, K, H, F, T, n_16=int(share16 * n), n_pages=n).routed
+    assert r.path == DECODE and r.mtb in (1, 2) and r.rt == rt
+
+
 def _one_copy(T, K, H, F):
     return T * K * (2 * F + 4 * H)
 

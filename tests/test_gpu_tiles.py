@@ -82,6 +82,27 @@ def test_decode_two_row_tiles(T, share16, H, G, act, sdt):
     L.close()
 
 
+@pytest.mark.parametrize("T,G", [(16, 128), (60, 64), (33, 256)])
+def test_row_tiles_give_the_same_bits(T, G):
+    """One or two row tiles per wave: two layers that differ only in the bitwidth
+    of the pages of two experts that no token uses (4, then 16 bits: a quarter
+    of the pages) run the two forms on the same pages."""
+    import torch
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], H=1024, F=2048, R=64, G=G, T=T, act=BF16, sdt=BF16)
+    lg = synth.logits(cfg).copy()
+    lg[:, 6:] -= 100.0
+    x, out = to_dev16(synth.activations(cfg)), []
+    for unused in (4, 16):
+        say("row tiles T=%d G=%d, unused pages at %d bits" % (T, G, unused))
+        bits = [np.array([[unused if e >= 6 else (8, 4)[(e + rb) % 2] for rb in range(cfg.nrb(p))]
+                          for e in range(cfg.E)], np.int32) for p in range(3)]
+        L = gpu_random_layer(cfg, bits=bits)
+        out.append(L.forward(x, L.route(to_dev(lg), cfg.K), out_fp32=True))
+        torch.cuda.synchronize()
+        L.close()
+    assert torch.equal(out[0], out[1])
+
+
 def test_narrow_tiles_keep_within_static_workspace():
     """100 slots per expert, 3200 slots of H = 4096: the SwiGLU rows and one copy
     of the down partials fit the allocation-free entry point's 64 MiB, two
