@@ -180,11 +180,12 @@ pw_status pw_route_topk(const float* logits, int T, int E, int K, int renorm,
  * token's last n_shared columns must be the shared experts (in order), its
  * first columns routed experts only. The GEMM runs the routed and the shared
  * experts as separate launches, each with the kernels suited to its slots
- * per expert (a shared expert has T). In layers of 256 MiB of pages or more
- * the shared experts' launches go to a stream of the layer's own, forked
- * from the caller's stream and joined back before the combine, so that they
- * run beside the routed ones (under graph capture: two branches); in smaller
- * layers, where the fork costs more than it hides, and with
+ * per expert (a shared expert has T). In layers of 256 MiB of pages or more,
+ * and in smaller ones where the batch (call by call) or the experts in use
+ * (under graph capture) make the step long enough to hide it, the shared
+ * experts' launches go to a stream of the layer's own, forked from the caller's
+ * stream and joined back before the combine, so that they run beside the
+ * routed ones (under graph capture: two branches); elsewhere, and with
  * pw_layer_set_chains(layer, 1), they follow them on the caller's stream.
  * That stream (default priority) and its two
  * events live on the pool's device (created with the layer by

@@ -589,8 +589,11 @@ pw_status pw_moe_paged_gemm(const pw_layer* Lc, const void* x, int T, int K, con
   Unit units[2];
   int nu = 0;
   const bool two = L->chains == 2 && L->side;
-  const bool shared_fork = two && pw::fork_shared(wl, L->st.alloc.used());
-  const bool split_routed = two && pw::fork_chains(wl, L->st.alloc.used()) && capturing(st);
+  const uint64_t pages = L->st.alloc.used();
+  const bool chains = two && pw::fork_chains(wl, pages);
+  const bool captured = two && (chains || wl.r[1].ne > 0) && capturing(st);
+  const bool shared_fork = two && pw::fork_shared(wl, L->st.desc, T, pages, captured);
+  const bool split_routed = chains && captured;
   if (split_routed) {
     units[0] = Unit{wl.r[0], st};
     units[0].r.ne = wl.r[0].ne / 2;

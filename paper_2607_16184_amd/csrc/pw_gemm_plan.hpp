@@ -203,32 +203,49 @@ inline WsLayout ws_layout(const pw_layer_desc& d, int T, int K, bool apl, int n_
 }
 
 // Whether a call forks work to the layer's own stream. A fork and join cost a
-// few microseconds in a graph and 10 to 40 issued call by call (two more
-// launches, two event records and two cross-stream waits), so:
-//   small layers (pages below kForkPages) never fork;
-//   shared experts fork above that: their few workgroups run beside the
-//     routed ones (60 + 4 experts of 2048 x 1408, 128 tokens: 164 us a step
-//     against 179 call by call, 157 against 184 in a graph; at 16 tokens 110
-//     either way and 104 against 114);
-//   the second routed chain forks only under stream capture, and where every
-//     expert expects a slot: in a graph it gains (8 experts of 4096 x 14336,
-//     64 tokens: 340 us against 351; 2048 x 7168: 111 against 114; tiny layer
-//     39 against 21), call by call it gains nothing (345 against 346) or loses
-//     (33 tokens on 4- and 8-bit pages 189 against 186, one token 112 against
-//     100, tiny layer 64 against 21).
+// few microseconds in a graph; call by call the launches, event records and
+// cross-stream waits take the host 60 to 70 us a step, which hides only behind
+// enough work. In layers of kForkPages or more every call may fork; below, the
+// shared experts fork where that pays, by what the step reads.
+//
+// Shared experts, whose few workgroups run beside the routed ones (one stream /
+// forked, us a step; page bytes and tokens):
+//   in a graph, from about 20 MiB of pages of experts in use (60 + 4 experts: 48
+//     MiB, 1 token 36 / 47, 4 41 / 47, 16 47 / 46, 64 63 / 56, 512 91 / 74; 96
+//     MiB, 1 40 / 47, 4 48 / 47, 128 74 / 67; 192 MiB, 1 47 / 48, 4 61 / 54; 16 + 1
+//     experts, 102 MiB, 1 54 / 47);
+//   call by call, from about 6400 MiB times tokens (60 + 4: 48 MiB, 256 tokens 71 /
+//     72, 512 86 / 80; 96 MiB, 128 71 / 73, 256 81 / 82, 1024 107 / 100; 192 MiB, 16
+//     64 / 71, 64 88 / 89, 256 108 / 95; 32 + 2, 51 MiB, 128 70 / 71, 256 80 / 73; 16 +
+//     1, 102 MiB, 16 61 / 69, 64 91 / 85; 64 + 1, 146 MiB, 16 57 / 71, 64 81 / 79);
+//   from kForkPages on always (288 MiB, 64 tokens 113 / 106, 512 166 / 152; 528 MiB,
+//     128 170 / 159; at a few tokens call by call it costs: 288 MiB, 1 token 54 / 71,
+//     16 82 / 85).
+// The second routed chain forks only under stream capture, in layers of
+// kForkPages or more and where every expert expects a slot. In a graph it gains
+// in large layers of few experts (one chain / two: 8 experts of 4096 x 14336, 16
+// tokens 342 / 336, 64 tokens 362 / 355; no 16-bit page, 4 tokens 134 / 129), is
+// even around 500 MiB (of 4096 x 4096, 557 MiB, 4 tokens 84 / 86, 16 118 / 116, 64
+// 130 / 127, 100 135 / 136; 64 experts of 2048 x 1408, 766 MiB, 16 tokens 122 / 123,
+// 64 158 / 159) and costs a little around 300 (of 2048 x 4096, 278 MiB, 16 tokens
+// 69 / 72, 64 80 / 79); call by call it loses (8 experts of 4096 x 14336, 64 tokens
+// 358 / 362; of 2048 x 4096 75 / 85).
 constexpr uint64_t kForkPages = uint64_t(256) << 20;
-
-inline bool may_fork(uint64_t pages) { return pages >= kForkPages; }
+constexpr uint64_t kForkGraphBytes = uint64_t(20) << 20;
+constexpr uint64_t kForkByteTokens = uint64_t(6400) << 20;
 
 // The shared experts' launches beside the routed ones.
-inline bool fork_shared(const WsLayout& w, uint64_t pages) {
-  return may_fork(pages) && w.r[0].ne > 0 && w.r[1].ne > 0;
+inline bool fork_shared(const WsLayout& w, const pw_layer_desc& d, int T, uint64_t pages, bool captured) {
+  if (w.r[0].ne <= 0 || w.r[1].ne <= 0) return false;
+  if (pages >= kForkPages) return true;
+  const uint64_t used = std::min<uint64_t>(d.E, w.r[0].S + static_cast<uint64_t>(w.r[1].ne));   // experts in use
+  return captured ? pages / d.E * used >= kForkGraphBytes : pages * static_cast<uint64_t>(T) >= kForkByteTokens;
 }
 
 // The routed range as two chains, under capture.
 inline bool fork_chains(const WsLayout& w, uint64_t pages) {
   const RangePlan& r = w.r[0];
-  return may_fork(pages) && w.r[1].ne <= 0 && r.path == GemmPath::kDecode && r.ne >= 2 &&
+  return pages >= kForkPages && w.r[1].ne <= 0 && r.path == GemmPath::kDecode && r.ne >= 2 &&
          r.S >= static_cast<size_t>(r.ne);
 }
 

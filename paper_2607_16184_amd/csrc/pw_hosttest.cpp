@@ -217,8 +217,8 @@ void pwt_host_stats(void* hv, uint64_t* capacity, uint64_t* used) {
 
 // The plan of one GEMM call that has ws_bytes of workspace: out[0] bytes needed, then per range (routed,
 // shared) experts, slots, path, K splits, 128-blocks per split, slot tiles per
-// pass and row tiles per wave; out[15] and out[16]: whether the shared range
-// and the routed chains fork.
+// pass and row tiles per wave; out[15 .. 17]: whether the shared range forks
+// call by call and in a graph, and whether the routed chains do (in a graph).
 void pwt_gemm_plan(const pw_layer_desc* d, int T, int K, int apl, int n_shared, uint64_t n_16, uint64_t n_pages,
                    uint64_t page_bytes, uint64_t ws_bytes, int64_t* out) {
   const pw::WsLayout w = pw::ws_layout(*d, T, K, apl != 0, n_shared, ws_bytes);
@@ -228,7 +228,7 @@ void pwt_gemm_plan(const pw_layer_desc* d, int T, int K, int apl, int n_shared, 
                           r.mtb, r.ne > 0 ? pw::row_tiles(*d, n_16, n_pages, r) : 0};
     for (int64_t x : v) *out++ = x;
   }
-  *out++ = pw::fork_shared(w, page_bytes) ? 1 : 0;
+  for (const bool captured : {false, true}) *out++ = pw::fork_shared(w, *d, T, page_bytes, captured) ? 1 : 0;
   *out++ = pw::fork_chains(w, page_bytes) ? 1 : 0;
 }
 

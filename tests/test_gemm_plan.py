@@ -30,12 +30,12 @@ class Plan:
         lib.pwt_gemm_plan.restype = None
         lib.pwt_gemm_plan.argtypes = ([ctypes.POINTER(Desc)] + [ctypes.c_int] * 4 + [ctypes.c_uint64] * 4
                                       + [ctypes.POINTER(ctypes.c_int64)])
-        out = (ctypes.c_int64 * 17)()
+        out = (ctypes.c_int64 * 18)()
         lib.pwt_gemm_plan(ctypes.byref(Desc(E, H, F, 64, 128, 1, 1)), T, K, int(apl), n_shared, n_16, n_pages, pages,
                           ws, out)
         self.total = out[0]
         self.routed, self.shared = Range(out[1:8]), Range(out[8:15])
-        self.fork_shared, self.fork_chains = bool(out[15]), bool(out[16])
+        self.fork_shared, self.fork_shared_graph, self.fork_chains = (bool(v) for v in out[15:18])
 
 
 @pytest.mark.parametrize("E,K,H,F,slots,path", [
@@ -75,6 +75,26 @@ def test_row_tiles_of_the_decode_kernels(E, K, H, F, T, share16, rt):
     n = E * (2 * F + H) // 64
     r = Plan(E, K, H, F, T, n_16=int(share16 * n), n_pages=n).routed
     assert r.path == DECODE and r.mtb in (1, 2) and r.rt == rt
+
+
+@pytest.mark.parametrize("E,n_shared,mib,T,eager,graph", [
+    (64, 4, 48, 1, False, False), (64, 4, 48, 4, False, False), (64, 4, 48, 16, False, True),
+    (64, 4, 48, 512, True, True), (64, 4, 96, 1, False, False), (64, 4, 96, 4, False, True),
+    (64, 4, 96, 64, False, True), (64, 4, 96, 1024, True, True), (64, 4, 192, 256, True, True),
+    (17, 1, 102, 1, False, True), (17, 1, 102, 64, True, True), (65, 1, 146, 16, False, True),
+    (64, 4, 256, 1, True, True), (64, 0, 528, 64, False, False),
+])
+def test_fork_of_the_shared_experts(E, n_shared, mib, T, eager, graph):
+    p = Plan(E, 4 + n_shared, 1024, 512, T, n_shared=n_shared, pages=mib << 20)
+    assert (p.fork_shared, p.fork_shared_graph) == (eager, graph)
+
+
+@pytest.mark.parametrize("E,K,mib,T,n_shared,fork", [
+    (8, 2, 256, 16, 0, True), (8, 2, 255, 16, 0, False), (8, 2, 256, 3, 0, False), (8, 2, 256, 4, 0, True),
+    (8, 2, 256, 200, 0, False), (10, 4, 256, 16, 2, False),
+])
+def test_fork_of_the_routed_chains(E, K, mib, T, n_shared, fork):
+    assert Plan(E, K, 1024, 2048, T, n_shared=n_shared, pages=mib << 20).fork_chains == fork
 
 
 def _one_copy(T, K, H, F):
