@@ -2,19 +2,28 @@
 replayed: every replay is bit-identical to the eager step, for each GEMM path
 (decode kernels, streaming kernel, LDS-tiled kernel), with eager work on the
 same stream between replays. Nothing in the step allocates or clears memory
-with a memset, so the captured launches are the eager ones."""
+with a memset, so the captured launches are the eager ones.
+
+Layers that are large enough fork work to a stream of their own (the second
+chain of the routed experts under capture, the shared experts): the last
+three tests take such layers; two of them hold pages of every format and look
+for the two branches in the captured graph."""
+import ctypes
+import dataclasses
+
 import numpy as np
 import pytest
 
-from helpers import case, gpu_layer, say, to_dev, to_dev16
-from paper_2607_16184_amd import synth
+from helpers import case, gpu_layer, gpu_random_layer, say, to_dev, to_dev16
+from paper_2607_16184_amd import pw, synth
+from test_gemm_plan import DECODE, STREAM, TILED, Plan
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("T,chains", [(16, 2), (16, 1), (300, 2), (1000, 2)])
 def test_graph_replay_matches_eager(T, chains):
-    """Captured with two chains (two graph branches at decode sizes) or one."""
+    """A small layer: one stream and one graph branch, whatever the chains."""
     import torch
     from paper_2607_16184_amd.layer import PagedLayer
     cfg, w16, bits, order = case("tiny", T=T)
@@ -54,10 +63,9 @@ def test_graph_replay_matches_eager(T, chains):
 
 @pytest.mark.parametrize("T", [16, 100])
 def test_graph_replay_shared_experts(T):
-    """A layer with shared experts: their GEMMs run on the layer's own stream,
-    forked from the caller's and joined before the combine, so the captured
-    graph has two branches. Every replay is bit-identical to the eager step,
-    with eager steps (which fork and join again) between the replays."""
+    """A small layer with shared experts, whose GEMMs follow the routed ones on
+    the caller's stream. Every replay is bit-identical to the eager step, with
+    eager steps between the replays."""
     import torch
     from paper_2607_16184_amd.layer import PagedLayer
     cfg, w16, bits, order = case("tiny_shared", T=T)
@@ -99,8 +107,8 @@ def test_graph_replay_shared_experts(T):
 
 @pytest.mark.parametrize("T", [16, 40, 100])
 def test_chains_bit_identical(T):
-    """The routed experts as one chain or as two concurrent chains (the
-    second on the layer's stream) give the same bits, 16-bit and fp32 out."""
+    """The chains setting changes no bits, 16-bit and fp32 out (here, in a small
+    layer, both settings launch alike), and takes 1 or 2 only."""
     import torch
     cfg, w16, bits, order = case("tiny", T=T)
     say("one chain vs two chains, tiny T=%d" % T)
@@ -123,10 +131,9 @@ def test_chains_bit_identical(T):
 
 @pytest.mark.parametrize("T,kw", [(16, {}), (100, {}), (600, dict(F=4096, n_shared=4, E=12))])
 def test_chains_bit_identical_shared(T, kw):
-    """With shared experts the shared range runs on the layer's stream beside
-    the routed one (two chains) or after it (one chain): same bits. T = 100
-    puts the shared range on the streaming kernel, T = 600 (4 shared experts
-    of F = 4096) on the tiled one."""
+    """The chains setting changes no bits with shared experts either (small
+    layers: both settings launch alike, but for the 600-token batch of four
+    shared experts, which forks call by call)."""
     import torch
     cfg, w16, bits, order = case("tiny_shared", T=T, **kw)
     say("one chain vs two chains with shared experts, T=%d" % T)
@@ -188,4 +195,91 @@ def test_forked_layer_stream_bit_identical(n_shared):
         step(other)                                        # eager work in between
         torch.cuda.synchronize()
         assert torch.equal(other, want), r
+    L.close()
+
+
+def _branches(graph):
+    """Whether some node of a captured graph has two successors."""
+    n = ctypes.c_size_t(0)
+    raw = ctypes.c_void_p(graph.raw_cuda_graph())
+    assert pw._lib.hipGraphGetEdges(raw, None, None, ctypes.byref(n)) == 0
+    src, dst = (ctypes.c_void_p * n.value)(), (ctypes.c_void_p * n.value)()
+    assert pw._lib.hipGraphGetEdges(raw, src, dst, ctypes.byref(n)) == 0
+    return len(set(src)) < n.value
+
+
+def _check_fork(L, cfg, T, eager_fork):
+    """One chain and two, call by call and captured, give the same bits; only
+    the capture with two chains has branches."""
+    import torch
+    from paper_2607_16184_amd.layer import PagedLayer
+    n = cfg.n_shared
+    L.set_shared_experts(n)
+    plan = Plan(cfg.E, cfg.K + n, cfg.H, cfg.F, T, n_shared=n, pages=L.stats()[0])
+    assert plan.fork_shared == eager_fork and (plan.fork_shared_graph if n else plan.fork_chains)
+    logits, x = to_dev(synth.logits(cfg)), to_dev16(synth.activations(cfg))
+    gate = to_dev(synth.shared_gate(cfg)) if n else None
+    rbuf = PagedLayer.routing_buffers(T, cfg.E, cfg.K + n)
+    y = torch.empty((T, cfg.H), dtype=torch.float32, device="cuda")
+
+    def step(out):
+        L.forward(x, L.route_shared(logits, cfg.K, n, gate=gate, out=rbuf), out_fp32=True, y=out)
+
+    L.set_chains(1)
+    step(y)
+    torch.cuda.synchronize()
+    want = y.clone()
+    assert bool(torch.isfinite(want).all())
+    other = torch.empty_like(y)
+    for chains in (1, 2):
+        L.set_chains(chains)
+        y.fill_(float("nan"))
+        step(y)
+        torch.cuda.synchronize()
+        assert torch.equal(y, want), chains
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        g = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(g, stream=side):
+            step(y)
+        assert _branches(g) == (chains == 2), chains
+        for r in range(3):
+            y.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(y, want), (chains, r)
+            step(other)                                    # eager work in between
+            torch.cuda.synchronize()
+            assert torch.equal(other, want), (chains, r)
+    return plan
+
+
+@pytest.mark.parametrize("T,mtb", [(16, 1), (64, 2), (130, 4)])
+def test_forked_chains_bit_identical(T, mtb):
+    """The second expert chain under capture, at one, two and four slot tiles per
+    pass, in a layer of 256 MiB of 16-, 8- and 4-bit pages."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], H=2048, F=5120, G=128, T=T, act=synth.BF16, sdt=synth.BF16)
+    say("forked chains, T=%d" % T)
+    L = gpu_random_layer(cfg)
+    assert L.stats()[0] >= 256 << 20
+    p = _check_fork(L, cfg, T, False)
+    assert p.routed.path == DECODE and p.routed.mtb == mtb
+    L.close()
+
+
+@pytest.mark.parametrize("T,E,n_shared,F,eager_fork,paths", [
+    (40, 10, 2, 2048, False, (DECODE, DECODE)),
+    (100, 10, 2, 2048, True, (DECODE, STREAM)),
+    (300, 10, 2, 2048, True, (STREAM, STREAM)),
+    (600, 12, 4, 4096, True, (TILED, TILED)),
+])
+def test_forked_shared_experts_bit_identical(T, E, n_shared, F, eager_fork, paths):
+    """The shared experts' launches on the layer's stream, on each GEMM kernel and
+    with pages of 16, 8 and 4 bits; call by call where the batch is large enough."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny_shared"], E=E, n_shared=n_shared, H=1024, F=F, G=128, T=T,
+                              act=synth.BF16, sdt=synth.BF16)
+    say("forked shared experts, T=%d" % T)
+    L = gpu_random_layer(cfg)
+    p = _check_fork(L, cfg, T, eager_fork)
+    assert (p.routed.path, p.shared.path) == paths
     L.close()

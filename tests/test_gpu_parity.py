@@ -239,11 +239,12 @@ def test_zero_up_projection_gives_zero():
     L.close()
 
 
-# Above 48 expected slots per expert the LDS-tiled GEMM runs (with 128- or
-# 256-slot tiles), or for down projections of other than 256-row multiples the
-# streaming GEMM; both feed quantized weights to the MFMA as fl32(z + c*s) rounded to
-# the activation dtype, so their fp32 output is compared with the oracle read
-# the same way (w_round).
+# Large per-expert slot counts (at least 128 expected per expert) take the
+# LDS-tiled GEMM with 256-slot tiles; medium ones (49..127) take it too where its
+# tiles fill the chip (tests/test_gpu_tiles.py), and in layers as small as these
+# the streaming GEMM with 64-slot tiles. Both feed quantized weights to the MFMA
+# as fl32(z + c*s) rounded to the activation dtype, so their fp32 output is
+# compared with the oracle read the same way (w_round).
 
 @pytest.mark.parametrize("T", [1000, 1531])
 def test_tiny_tiled_path_parity(T):
@@ -275,7 +276,7 @@ def test_tiny_tiled_uniform_and_empty_experts(b):
 
 @pytest.mark.parametrize("T", [300, 211])
 def test_tiny_stream_path_parity(T):
-    """49..120 expected slots per expert: the tiled GEMM's 128-slot tiles."""
+    """49..127 expected slots per expert: the streaming GEMM (64-slot tiles)."""
     cfg, w16, bits, order = case("tiny", T=T)
     say("tiny stream T=%d" % T)
     L = gpu_layer(cfg, w16, bits, order)
@@ -288,7 +289,7 @@ def test_tiny_stream_path_parity(T):
 @pytest.mark.parametrize("b", [16, 8, 4])
 def test_tiny_stream_uniform_and_empty_experts(b):
     """Every page at one bitwidth; 200 tokens all routed to experts 3 and 5
-    (two 128-slot tiles each, the last ragged; six experts with none)."""
+    (four 64-slot tiles each, the last ragged; six experts with none)."""
     cfg, w16, _, order = case("tiny", T=200)
     bits = [np.full((cfg.E, cfg.nrb(p)), b, np.int32) for p in range(3)]
     lg = synth.logits(cfg).copy()
