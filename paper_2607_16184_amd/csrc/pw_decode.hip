@@ -16,19 +16,16 @@
 // as an exact 16-bit float (int8 codes through an exact conversion; int4
 // codes, and int8 codes with fp16 activations, OR-ed into the mantissa of a
 // constant OFF, giving OFF + c exactly). Per group of G along K the MFMA gives
-// P = sum (c + OFF) x and X = sum x; the group's scale s and zero z are then
-// applied in fp32 on the accumulator: acc += s * P + (z - OFF * s) * X, which
-// is sum (z + c s) x. Weights are never rounded: z + c*s enters exactly.
-//
-// X. With one or two slot tiles per pass, X is one more MFMA per k-step, an
-// operand of ones against the activations already read for P (every row of
-// the result is the slot's sum, the layout the correction needs); it replaces
-// dot products, cross-lane sums, LDS writes and reads that cost an int4 wave
-// about a fifth of its instructions (all pages int4, 64 tokens on 8 experts
-// of 4096 x 14336: gate/up 143 -> 135 us, down 78 -> 73; half the pages at 16
-// bits: 229 -> 227). With more slot tiles the extra accumulators cost more
-// (64 experts, 512 tokens: gate/up 100 -> 102 us): X comes from sums taken
-// while the activations are staged.
+// P = sum (c + OFF) x, and X = sum x comes from sums taken while the
+// activations are staged; the group's scale s and zero z are then applied in
+// fp32 on the accumulator: acc += s * P + (z - OFF * s) * X, which is
+// sum (z + c s) x. Weights are never rounded: z + c*s enters exactly. (X as one
+// more MFMA per k-step, ones against the activations, would take a fifth of an
+// int4 wave's instructions away, but it is one running fp32 sum over the group:
+// large values of either sign cut the small ones short, and on normal data the
+// down projection's error against 64 bits grows, by 0.5 % with bf16 and 4 % with
+// fp16 activations of 8 experts of 4096 x 14336. The staged sums cost 1 to 2 % of
+// a step without 16-bit pages: 33 tokens 176 -> 178 us, 64 tokens 200 -> 202.)
 #include "pw_device.hpp"
 #include "pw_internal.hpp"
 
@@ -57,17 +54,6 @@ __device__ __forceinline__ float hi16(uint32_t h) {
   if constexpr (FMT == PW_BF16) return __uint_as_float(h & 0xFFFF0000u);
   else return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(h >> 16)));
 }
-
-// A slot tile's activation sum X: an MFMA accumulator (up to two slot tiles
-// per pass) or a sum read from the staged chunk (see the file comment).
-template <int NT> constexpr bool mfma_sums() { return NT <= 2; }
-template <bool M> struct XSum { typedef f32x4 type; };
-template <> struct XSum<false> { typedef float type; };
-template <int NT> using xsum_t = typename XSum<mfma_sums<NT>()>::type;
-__device__ __forceinline__ float xsum_val(f32x4 x) { return x[0]; }
-__device__ __forceinline__ float xsum_val(float x) { return x; }
-__device__ __forceinline__ void xsum_clear(f32x4& x) { x = f32x4{0.f, 0.f, 0.f, 0.f}; }
-__device__ __forceinline__ void xsum_clear(float& x) { x = 0.0f; }
 
 template <int B> struct WF;
 template <> struct WF<16> { u32x4 v[4]; };
@@ -123,10 +109,10 @@ __device__ __forceinline__ u32x4 wf_op(const WF<B>& f, int i, uint32_t magic) {
 template <int ACT> constexpr uint32_t code_magic() { return ACT == PW_BF16 ? 0x43004300u : 0x64006400u; }
 
 // acc += s * P + (z - OFF s) * X for the lane's four rows (two fused
-// multiply-adds per row). xs[t] is the group's activation sum X for this
-// lane's slot (tile t).
+// multiply-adds per row). X[t] is the group's activation sum for this lane's
+// slot (tile t).
 template <int ACT, int SDT, int B, int NT>
-__device__ __forceinline__ void group_fix(f32x4 (&acc)[NT], const f32x4 (&p)[NT], const xsum_t<NT> (&xs)[NT], u32x4 sz) {
+__device__ __forceinline__ void group_fix(f32x4 (&acc)[NT], const f32x4 (&p)[NT], const float (&xs)[NT], u32x4 sz) {
   constexpr float off = CodeOff<ACT, B>::value;
   float s[4], zp[4];
 #pragma unroll
@@ -139,7 +125,7 @@ __device__ __forceinline__ void group_fix(f32x4 (&acc)[NT], const f32x4 (&p)[NT]
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       acc[t][r] = __builtin_fmaf(s[r], p[t][r], acc[t][r]);
-      acc[t][r] = __builtin_fmaf(zp[r], xsum_val(xs[t]), acc[t][r]);
+      acc[t][r] = __builtin_fmaf(zp[r], xs[t], acc[t][r]);
     }
   }
 }
@@ -159,10 +145,10 @@ __device__ __forceinline__ void group_fix(f32x4 (&acc)[NT], const f32x4 (&p)[NT]
 constexpr int kCK = 2;                            // 128-blocks per chunk
 constexpr int kXRow = kCK * 128 * 2 + 16;         // LDS bytes per staged activation row
 
-// Per chunk buffer: NT*16 staged rows, then (without MFMA sums) NT*16 x
-// (2 kCK) fp32 sums of 64-value half blocks (the X of each group).
+// Per chunk buffer: NT*16 staged rows, then NT*16 x (2 kCK) fp32 sums of
+// 64-value half blocks (the code-domain X of each quantization group).
 template <int NT>
-constexpr int xbuf_bytes() { return NT * 16 * kXRow + (mfma_sums<NT>() ? 0 : NT * 16 * 2 * kCK * 4); }
+constexpr int xbuf_bytes() { return NT * 16 * kXRow + NT * 16 * 2 * kCK * 4; }
 template <int NT>
 constexpr int lds_x_bytes() { return 2 * xbuf_bytes<NT>(); }
 
@@ -274,16 +260,16 @@ __device__ __forceinline__ float sum8(float v) {
   return v;
 }
 
-// Writes the staged rows and, when a quantized page reads them and X is not an
-// MFMA result, per row the sums of each 64-value half block (8 consecutive
-// pieces held by 8 consecutive lanes).
+// Writes the staged rows and, when a quantized page reads them, per row the
+// sums of each 64-value half block (8 consecutive pieces held by 8
+// consecutive lanes).
 template <int ACT, int NT, int NW>
 __device__ __forceinline__ void x_store(const XStage<NT, NW>& s, uint8_t* buf, bool sums) {
   const int col = threadIdx.x % kPieces;
 #pragma unroll
   for (int j = 0; j < x_passes<NT, NW>(); ++j)
     *reinterpret_cast<u32x4*>(buf + x_row<NW>(j) * kXRow + col * 16) = s.v[j];
-  if (!mfma_sums<NT>() && sums) {
+  if (sums) {
     float* hs = reinterpret_cast<float*>(buf + NT * 16 * kXRow);
 #pragma unroll
     for (int j = 0; j < x_passes<NT, NW>(); ++j) {
@@ -307,7 +293,7 @@ __device__ __forceinline__ void lds_barrier() {
 template <int ACT, int SDT, int B, int NT, int GK, int RT>
 __device__ __forceinline__ void compute_block(const Slot<B, GK, RT>& sl, const uint8_t* xblk, const float* hsum,
                                               int hb0, bool gend, uint32_t magic, f32x4 (&acc)[RT][NT],
-                                              f32x4 (&p)[RT][NT], xsum_t<NT> (&xs)[NT]) {
+                                              f32x4 (&p)[RT][NT], float (&xs)[NT]) {
   const int lane = lane_id(), lc = lane & 15, lg = lane >> 4;
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -324,14 +310,12 @@ __device__ __forceinline__ void compute_block(const Slot<B, GK, RT>& sl, const u
         if constexpr (B == 16) acc[rt][t] = mma<ACT>(aw[rt], bx, acc[rt][t]);
         else p[rt][t] = mma<ACT>(aw[rt], bx, fresh ? zero : p[rt][t]);
       }
-      if constexpr (B != 16 && mfma_sums<NT>()) xs[t] = mma<ACT>(ones_op<ACT>(), bx, fresh ? zero : xs[t]);
     }
     if constexpr (B != 16) {
       if constexpr (GK == kG64) {
         if (i & 1) {
 #pragma unroll
-          for (int t = 0; t < NT; ++t)
-            if constexpr (!mfma_sums<NT>()) xs[t] = hsum[(t * 16 + lc) * (2 * kCK) + hb0 + (i >> 1)];
+          for (int t = 0; t < NT; ++t) xs[t] = hsum[(t * 16 + lc) * (2 * kCK) + hb0 + (i >> 1)];
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) group_fix<ACT, SDT, B, NT>(acc[rt], p[rt], xs, sl.sz[rt][i >> 1]);
         }
@@ -339,15 +323,14 @@ __device__ __forceinline__ void compute_block(const Slot<B, GK, RT>& sl, const u
         if (i == 3) {
 #pragma unroll
           for (int t = 0; t < NT; ++t)
-            if constexpr (!mfma_sums<NT>())
-              xs[t] = hsum[(t * 16 + lc) * (2 * kCK) + hb0] + hsum[(t * 16 + lc) * (2 * kCK) + hb0 + 1];
+            xs[t] = hsum[(t * 16 + lc) * (2 * kCK) + hb0] + hsum[(t * 16 + lc) * (2 * kCK) + hb0 + 1];
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) group_fix<ACT, SDT, B, NT>(acc[rt], p[rt], xs, sl.sz[rt][0]);
         }
       } else if (i == 3) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
-          if constexpr (!mfma_sums<NT>()) xs[t] += hsum[(t * 16 + lc) * (2 * kCK) + hb0] + hsum[(t * 16 + lc) * (2 * kCK) + hb0 + 1];
+          xs[t] += hsum[(t * 16 + lc) * (2 * kCK) + hb0] + hsum[(t * 16 + lc) * (2 * kCK) + hb0 + 1];
         if (gend) {
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) {
@@ -356,7 +339,7 @@ __device__ __forceinline__ void compute_block(const Slot<B, GK, RT>& sl, const u
             for (int t = 0; t < NT; ++t) p[rt][t] = zero;
           }
 #pragma unroll
-          for (int t = 0; t < NT; ++t) xsum_clear(xs[t]);
+          for (int t = 0; t < NT; ++t) xs[t] = 0.0f;
         }
       }
     }
@@ -382,12 +365,12 @@ __device__ void wave_gemm(uint8_t* lds, const uint8_t* xbase, const uint32_t (&r
   uint32_t magic = code_magic<ACT>();
   asm volatile("" : "+v"(magic));
   f32x4 p[RT][NT];
-  xsum_t<NT> xs[NT];
+  float xs[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) acc[rt][t] = p[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    xsum_clear(xs[t]);
+    xs[t] = 0.0f;
   }
   Slot<B, GK, RT> win[W];
   XStage<NT, NW> xr;

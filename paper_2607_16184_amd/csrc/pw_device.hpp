@@ -92,12 +92,6 @@ __device__ __forceinline__ f32x4 mma(u32x4 a, u32x4 b, f32x4 c) {
                                                   __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 
-template <int ACT>
-__device__ __forceinline__ u32x4 ones_op() {
-  const uint32_t one = ACT == PW_BF16 ? 0x3F803F80u : 0x3C003C00u;
-  return u32x4{one, one, one, one};
-}
-
 __device__ __forceinline__ u32x4 ld16(const uint8_t* p) { return *reinterpret_cast<const u32x4*>(p); }
 // Weights are streamed once: nontemporal loads.
 __device__ __forceinline__ u32x4 ld16_nt(const uint8_t* p) {

@@ -182,3 +182,36 @@ def test_swiglu_over_the_exponent_range():
     e = rel_err(got, O.forward(x16, ids, w, h_round=True, w_round=True))
     assert e <= 1e-3, e
     L.close()
+
+
+@pytest.mark.parametrize("act", [F16, BF16])
+@pytest.mark.parametrize("T", [16, 60, 130])
+def test_activation_sums_by_half_blocks(T, act):
+    """The decode kernels' activation sums X add 64-value half blocks on their own
+    before they meet: 2^15 and -2^15 in the second half leave nothing of
+    themselves in the sum of small values of the first (one running fp32 sum
+    would cut those to multiples of 2^-8, X by up to 2^-9). Gate and up pages of
+    ones (every group: scale 0, zero 1) make both projections X, so the SwiGLU
+    rows are silu(X) X: two roundings to 16 bits apart at most, and 64
+    roundings to fp32 inside X."""
+    import torch
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], E=4, K=1, R=64, G=128, T=T, act=act, sdt=act)
+    say("activation sums T=%d act=%d" % (T, act))
+    ones = np.full((4, cfg.F, cfg.H), synth.to16(np.ones(1, np.float32), act)[0])
+    bits = [np.array([[(8, 4)[rb % 2] for rb in range(cfg.nrb(p))]] * 4, np.int32) for p in range(3)]
+    L = gpu_layer(cfg, [ones, ones, synth.expert_weights(cfg, 2)], bits, synth.pool_order(cfg))
+    x = np.zeros((T, cfg.H), np.float32)
+    x[:, :64] = 0.125 * np.random.default_rng(7).standard_normal((T, 64))
+    x[:, 70], x[:, 100] = 32768.0, -32768.0
+    x16 = synth.to16(x, act)
+    routing = L.route(to_dev(synth.logits(cfg)), 1)
+    L.forward(to_dev16(x16), routing, out_fp32=True)
+    torch.cuda.synchronize()
+    got = np.empty((T, cfg.F))
+    got[routing[3].cpu().numpy()] = synth.from16(L.hidden_rows(T, 1).cpu().numpy().view(np.uint16), act)
+    X = synth.from16(x16, act).astype(np.float64).sum(1)
+    want = (X * X / (1.0 + np.exp(-X)))[:, None]
+    assert (got == got[:, :1]).all()
+    ulp, dx = (2.0 ** -10 if act == F16 else 2.0 ** -7), 64 * 2.0 ** -24
+    assert np.all(np.abs(got - want) <= ulp * np.abs(want) + 2.0 * dx * np.abs(X)[:, None]), np.abs(got / want - 1.0).max()
+    L.close()
