@@ -429,7 +429,10 @@ pw_status pw_layer_load_pages_apl(pw_layer* layer, int n, const int* e, const in
  *   stats[5 e + 0] = sum r        stats[5 e + 1] = number of slots
  *   stats[5 e + 2] = sum r |x|    stats[5 e + 3] = sum r |x|^2
  *   stats[5 e + 4] = max |x|
- * in float64 with a fixed summation order (bit-identical across runs).
+ * in float64 with a summation order fixed by the shapes (bit-identical across
+ * runs). A row's norm is summed in one order below 8192 rows and in another
+ * from there on: the last bits of the sums over the same rows may differ
+ * between calls of fewer and of more rows.
  * rows: [n_rows][dim] 16-bit values of dtype act (16-byte aligned, dim a
  * multiple of 8). rows_by_position = 0: the row of slot s = t K + k is
  * token t (the gate/up input x, n_rows = T); 1: the row of the i-th slot

@@ -7,6 +7,8 @@ ulps of exp); norms and their maximum to 1e-12; accumulation over calls;
 run-to-run bit identity; and an end-to-end step where the library's plan
 equals the oracle planner's, and the requantized pages are bit-exact.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -55,6 +57,25 @@ def test_routing_stats_gate_up_input(name):
     a, b = acc.cpu().numpy(), st.cpu().numpy()
     np.testing.assert_array_equal(a[:, [0, 1, 2, 3]], 2 * b[:, [0, 1, 2, 3]])
     np.testing.assert_array_equal(a[:, 4], b[:, 4])
+    L.close()
+
+
+@pytest.mark.parametrize("T,H", [(8191, 264), (8192, 512), (8195, 264), (8197, 520)])
+def test_routing_stats_of_many_rows(T, H):
+    """Four waves per row below 8192 rows, one from there on (with odd row
+    counts, and rows of no whole number of 512-value spans)."""
+    import torch
+    from paper_2607_16184_amd.layer import PagedLayer
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], K=1, T=T)
+    say("routing stats of %d rows of %d" % (T, H))
+    L = PagedLayer(cfg, 1 << 20)
+    logits = synth.logits(cfg)
+    routing = L.route(to_dev(logits), 1)
+    x16 = synth.to16(np.random.default_rng(12).standard_normal((T, H)).astype(np.float32), cfg.act)
+    st = L.routing_stats(to_dev16(x16), routing)
+    torch.cuda.synchronize()
+    x64 = synth.from16(x16, cfg.act).astype(np.float64)
+    _compare(st.cpu().numpy(), _oracle_stats(x64, lambda ss, off: ss, logits, 1, cfg.E))
     L.close()
 
 

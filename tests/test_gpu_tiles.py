@@ -19,6 +19,7 @@ import pytest
 import oracle
 from helpers import gpu_layer, gpu_random_layer, oracle_layer, rel_err, say, to_dev, to_dev16
 from paper_2607_16184_amd import synth
+from test_gemm_plan import DECODE, STREAM, TILED, Plan
 
 pytestmark = pytest.mark.gpu
 
@@ -35,6 +36,7 @@ F16, BF16 = synth.F16, synth.BF16
     ((500, 16, 17, 15), 256, 640, 64, 64, BF16, BF16),      # skew: idle waves in most tiles
     ((300, 129, 240, 1), 768, 128, 128, 128, F16, BF16),    # K = 128: one block per row of the down pages
     ((100, 90, 70, 120), 384, 256, 64, 64, BF16, BF16),     # H not a multiple of 256: the streaming kernel
+    (tuple(37 * e % 101 for e in range(130)), 256, 256, 64, 64, BF16, BF16),   # the tile search passes 64 experts twice
 ])
 def test_tile_edges(counts, H, F, R, G, act, sdt):
     import torch
@@ -159,6 +161,60 @@ def test_split_follows_the_workspace():
     torch.cuda.synchronize()
     assert torch.equal(small, static)
     assert rel_err(small.cpu().numpy(), split.cpu().numpy()) <= 1e-5
+    L.close()
+
+
+# Gates of the SwiGLU test: the linear part of the sigmoid, its tails, where
+# exp(-g) and 1 + exp(-g) leave the normal range, and beyond it.
+GATES = [0.0, 1e-20, -1e-20, 0.01, -0.01, 0.7, -0.7, 2.5, -2.5, 5.0, -5.0, 12.0, -12.0, 20.0, -20.0, 40.0, -40.0, 60.0, -60.0,
+         80.0, -80.0, 86.5, -86.5, 87.5, -87.5, 88.5, -88.5, 89.5, -89.5, 95.0, -95.0, 300.0, -300.0, 1e30, -1e30,
+         float("inf"), float("-inf"), float("nan")]
+
+
+@pytest.mark.parametrize("T,F,path", [(40, 512, DECODE), (60, 512, DECODE), (130, 512, DECODE), (240, 512, STREAM),
+                                      (240, 8192, TILED), (600, 512, TILED)])
+def test_swiglu_rows_by_element(T, F, path):
+    """The SwiGLU rows element by element over given gates, on every GEMM path
+    (the tiled one with either tile). Column 0 of x times 4 is the gate (twice
+    the largest bf16 makes it infinite) and column 1 the up value, through
+    16-bit pages that are zero elsewhere, so both reach SwiGLU exact (a NaN
+    gate comes with a NaN up). silu(g) u in fp32 is within a few 2^-24 of the
+    value and is then rounded to bf16: at most one step apart, 2^-7 of the
+    value, and 1 / (1 + exp(-g)) may vanish where it is below 2^-126."""
+    import torch
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], E=4, K=1, F=F, T=T, act=BF16, sdt=BF16)
+    assert Plan(4, 1, cfg.H, F, T).routed.path == path
+    say("swiglu rows T=%d F=%d" % (T, F))
+    w = [np.zeros((4, F, 256), np.float32), np.zeros((4, F, 256), np.float32), np.zeros((4, 256, F), np.float32)]
+    w[0][:, :, 0] = 4.0
+    w[1][:, :, 1] = np.array([1.0, -0.75])[np.arange(F) % 2]
+    bits = [np.full((4, cfg.nrb(p)), 16, np.int32) for p in range(3)]
+    L = gpu_layer(cfg, [synth.to16(v, BF16) for v in w], bits, synth.pool_order(cfg))
+    x = np.zeros((T, 256), np.float32)
+    g = np.array([GATES[t % len(GATES)] for t in range(T)], np.float32)
+    x[:, 0] = np.where(np.isinf(g), np.sign(g) * np.float32(3e38), g / 4)
+    x[:, 1] = np.array([1.0, -3.0, 0.125])[np.arange(T) // len(GATES) % 3]
+    x16 = synth.to16(x, BF16)
+    lg = np.zeros((T, 4), np.float32)
+    lg[np.arange(T), np.arange(T) % 4] = 100.0
+    routing = L.route(to_dev(lg), 1)
+    L.forward(to_dev16(x16), routing, out_fp32=True)
+    torch.cuda.synchronize()
+    rows = L.hidden_rows(T, 1).cpu().numpy().view(np.uint16)
+    got = np.empty((T, F), np.float64)
+    got[routing[3].cpu().numpy()] = synth.from16(rows, BF16)
+    xs = synth.from16(x16, BF16)
+    with np.errstate(all="ignore"):
+        gate = (xs[:, 0] * np.float32(4)).astype(np.float64)[:, None]          # overflows in fp32 as in the kernels
+        up = xs[:, 1].astype(np.float64)[:, None] * w[1][0, :, 1].astype(np.float64) + 0.0 * xs[:, :1]
+        want = gate / (1.0 + np.exp(-gate)) * up
+        want[(gate < -89.0)[:, 0] & np.isfinite(gate)[:, 0]] = 0.0             # exp(-g) is infinite in fp32
+        bad, inf = np.isnan(want), np.isinf(want)
+        assert bad.any() and inf.any()
+        assert np.array_equal(np.isnan(got), bad)
+        assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf])
+        wrong = np.abs(got - want) > 2.0 ** -7 * np.abs(want) + 90.0 * 2.0 ** -126 * np.abs(up)
+        assert not wrong[~inf].any(), gate[wrong.any(axis=1), 0]
     L.close()
 
 
