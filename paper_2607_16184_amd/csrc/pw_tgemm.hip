@@ -49,7 +49,6 @@ constexpr int kStK = 32;                    // K per stage: one MFMA k-step
 constexpr int kRing = 4;                    // weight stages in LDS
 constexpr int kTK = 64;                     // K per stage of the streaming kernel
 constexpr int kGN = 4;                      // weight blocks per group of tiles
-constexpr int kSgGN = 4;                    // weight blocks per raster band of the streaming kernel
 
 // A wave's weight share of a stage: 32 rows (two 16-row tiles) of one page as
 // four fragments f = 2 * tile + step.
@@ -121,21 +120,12 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
   else return __builtin_bit_cast(uint32_t, __builtin_convertvector(p, h2));
 }
 
-// Eight fp32 values -> four packed 16-bit words (round to nearest even).
+// Eight fp32 values -> four packed 16-bit words.
 template <int ACT>
 __device__ __forceinline__ u32x4 pack8(const float (&v)[8]) {
-  typedef float f2 __attribute__((ext_vector_type(2)));
-  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
   u32x4 o;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const f2 p = {v[2 * q], v[2 * q + 1]};
-    if constexpr (ACT == PW_BF16)
-      o[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(p, b2));
-    else
-      o[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector(p, h2));
-  }
+  for (int q = 0; q < 4; ++q) o[q] = pack2<ACT>(v[2 * q], v[2 * q + 1]);
   return o;
 }
 
@@ -787,8 +777,8 @@ __global__ __launch_bounds__(256) void k_sgemm(const GemmArgs a, int nblk, int m
   const int split = blockIdx.x / per_split, bid = blockIdx.x % per_split;
   const int per_xcd = per_split / 8;
   const int logical = (bid % 8) * per_xcd + bid / 8;
-  const int band = logical / (kSgGN * mtmax), inb = logical % (kSgGN * mtmax);
-  const int nb = band * kSgGN + inb % kSgGN, mt = inb / kSgGN;
+  const int band = logical / (kGN * mtmax), inb = logical % (kGN * mtmax);
+  const int nb = band * kGN + inb % kGN, mt = inb / kGN;
   if (nb >= nblk) return;
   int e = 0, off_e = 0, n_e = 0, m0 = 0;
   {
@@ -925,7 +915,7 @@ template <int ACT, int SDT, int MT>
 void sgemm_go(const GemmArgs& a, bool gateup, hipStream_t st) {
   const int nblk = gateup ? a.F / 64 : a.H / 128;
   const int mtmax = (a.s_range + MT - 1) / MT + a.ne;
-  const int n = ((nblk + kSgGN - 1) / kSgGN * kSgGN * mtmax + 7) / 8 * 8 * (gateup ? 1 : a.nsplit);
+  const int n = ((nblk + kGN - 1) / kGN * kGN * mtmax + 7) / 8 * 8 * (gateup ? 1 : a.nsplit);
   if (a.apl) {
     if (gateup)
       hipLaunchKernelGGL((k_sgemm<ACT, SDT, true, MT, true>), dim3(n), dim3(256), 0, st, a, nblk, mtmax);
