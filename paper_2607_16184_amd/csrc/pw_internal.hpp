@@ -127,9 +127,11 @@ hipError_t launch_clear_table(pw_page_entry* table, size_t n, hipStream_t st);
 hipError_t launch_gateup(const GemmArgs& a, hipStream_t st);
 hipError_t launch_down(const GemmArgs& a, hipStream_t st);
 hipError_t launch_combine(const GemmArgs& a, hipStream_t st);
-// more than 48 slots per expert: LDS-tiled GEMM (256 rows x 128 or 256 slots)
+// more than 48 slots per expert where the tiles fill the chip, any from 128 on:
+// LDS-tiled GEMM (256 rows x 128 or 256 slots)
 hipError_t launch_tgemm(const GemmArgs& a, bool gateup, hipStream_t st);
-// bit-plane layers and narrow shapes: register-streamed tiles of 32/64 slots
+// bit-plane layers, few experts and narrow shapes: register-streamed tiles of
+// 32 or 64 slots
 hipError_t launch_sgemm(const GemmArgs& a, bool gateup, hipStream_t st);
 hipError_t launch_apl_quant(const AplBatch& b, hipStream_t st);
 // ceiling probes: a plain streaming read and back-to-back bf16 MFMAs

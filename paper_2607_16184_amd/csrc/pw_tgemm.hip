@@ -672,8 +672,8 @@ __global__ __launch_bounds__(64 * kWaves) void k_tgemm(const GemmArgs a, int nbl
 }
 
 // ---------------------------------------------------------------------------
-// Streaming paged GEMM for small and medium per-expert slot counts
-// (bit-plane layers above all): HBM-bound, so the design goal is bytes in flight.
+// Streaming paged GEMM for medium per-expert slot counts of few experts, and for
+// bit-plane layers at any: HBM-bound, so the design goal is bytes in flight.
 // A workgroup of 4 waves covers 128 weight rows (gate/up: 64 rows of gate and
 // the same 64 rows of up; down: 128 rows) and MT slots of one expert. Each wave
 // streams 32 rows of one page through a register ring of D stages (64 values
@@ -971,8 +971,8 @@ hipError_t launch_tgemm(const GemmArgs& a, bool gateup, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Streaming path (32- or 64-slot tiles): bit-plane layers, few shared experts,
-// and shapes that the tiled kernel does not take.
+// Streaming path (32- or 64-slot tiles): bit-plane layers, experts too few for
+// the tiled kernel's tiles to fill the chip, and shapes that it does not take.
 hipError_t launch_sgemm(const GemmArgs& a, bool gateup, hipStream_t st) {
   if (a.ne <= 0) return hipSuccess;
   if (a.act == PW_BF16) {

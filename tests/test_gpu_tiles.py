@@ -109,7 +109,8 @@ def test_narrow_tiles_keep_within_static_workspace():
     """100 slots per expert, 3200 slots of H = 4096: the SwiGLU rows and one copy
     of the down partials fit the allocation-free entry point's 64 MiB, two
     copies would not, so the call is taken with one and gives the same bits as
-    with a workspace of the caller's."""
+    with a workspace of the caller's. (32 gate/up tiles: the streaming kernel;
+    test_split_follows_the_workspace has the tiled one.)"""
     import torch
     from paper_2607_16184_amd import pw
     cfg = dataclasses.replace(synth.CONFIGS["tiny"], E=32, K=1, H=4096, F=128, T=3200, act=BF16, sdt=BF16)
