@@ -157,18 +157,19 @@ inline RangePlan plan_range(const pw_layer_desc& d, int e0, int ne, size_t S, si
 //   at two slot tiles, at most an eighth of the pages are 16-bit (one / two, us
 //   a step: 8 experts of 4096 x 14336, 64 tokens, no 16-bit page 231 / 202, 12 %
 //   253 / 241, 25 % 284 / 281, 50 % 347 / 357; of 4096 x 4096, 12 % 96 / 93);
-//   at one, the share of 16-bit pages times H is at most 128 (9 slots per expert,
-//   25 % of the pages 8-bit: 8 experts of 4096 x 14336, none 207 / 184, 3 % 208 /
-//   204, 6 % 213 / 217, 12 % 230 / 238; 16 of 4096 x 2048, none 79 / 73, 3 % 78 / 81,
-//   12 % 89 / 93; 8 of 2048 x 4096, none 49 / 45, 6 % 51 / 49, 12 % 54.5 / 55.1; 64
-//   of 1024 x 1408, none 72 / 62, 6 % 76 / 68, 12 % 80 / 74), and every expert
-//   expects two slots or more (4 tokens: 8 of 4096 x 4096 53 / 55, one token of
-//   4096 x 14336 62 / 66).
+//   at one, the share of 16-bit pages times H is at most 128 up to H = 2048, and 96
+//   above (9 slots per expert, 25 % of the pages 8-bit: 8 experts of 4096 x 14336,
+//   none 207 / 184, 2 % 203 / 200, 3 % 208 / 204, 6 % 213 / 217, 12 % 230 / 238, of
+//   4096 x 4096, 2 % 76 / 72, and with 4 slots 3 % 72 / 75; 16 of 4096 x 2048, none
+//   79 / 73, 3 % 78 / 81, 12 % 89 / 93; 8 of 2048 x 4096, none 49 / 45, 6 % 51 / 49,
+//   12 % 54.5 / 55.1; 64 of 1024 x 1408, none 72 / 62, 6 % 76 / 68, 12 % 80 / 74), and
+//   every expert expects two slots or more (4 tokens: 8 of 4096 x 4096 53 / 55, one
+//   token of 4096 x 14336 62 / 66).
 inline int row_tiles(const pw_layer_desc& d, size_t n_16, size_t n_pages, const RangePlan& r) {
   const size_t ne = static_cast<size_t>(r.ne);
   if (ne * (d.F / 64) < kCUs) return 1;
   if (r.mtb == 2) return n_16 * 8 <= n_pages ? 2 : 1;
-  return n_16 * d.H <= 128 * n_pages && r.S >= 2 * ne ? 2 : 1;
+  return n_16 * d.H <= (d.H <= 2048 ? 128 : 96) * n_pages && r.S >= 2 * ne ? 2 : 1;
 }
 
 // The workspace of a call that has `ws_bytes` of it. A tiled range below

@@ -66,6 +66,7 @@ def test_down_splits_of_the_tiled_kernel(E, K, H, F, slots, nsplit):
 
 @pytest.mark.parametrize("E,K,H,F,T,share16,rt", [
     (8, 2, 4096, 14336, 33, 0.0, 2), (8, 2, 4096, 14336, 33, 0.06, 1), (8, 2, 4096, 4096, 16, 0.1, 1),
+    (8, 2, 4096, 4096, 16, 0.02, 2), (8, 2, 4096, 4096, 16, 0.03, 1),
     (8, 2, 4096, 4096, 4, 0.0, 1), (8, 2, 4096, 4096, 48, 0.0, 2), (64, 6, 2048, 1408, 33, 0.06, 2),
     (64, 6, 2048, 1408, 33, 0.07, 1), (64, 6, 1024, 1408, 33, 0.12, 2), (64, 6, 1024, 1408, 33, 0.13, 1),
     (8, 2, 4096, 14336, 64, 0.0, 2), (8, 2, 4096, 14336, 64, 0.12, 2), (8, 2, 4096, 14336, 64, 0.13, 1),   # two slot tiles
