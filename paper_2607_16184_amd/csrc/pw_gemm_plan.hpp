@@ -49,6 +49,32 @@ constexpr int kTileNarrow = 120;
 // Below this many slots per expert an expert's slots are about one tile.
 constexpr int kOneTileBelow = 128;
 
+// Whether a routed range of 49 to 127 slots per expert runs the tiled kernel, by
+// its gate/up tiles (`blocks`: one per expert and 128 rows of F). Figures:
+// streaming / tiled, us a step, 25 % of the pages at 16 and at 8 bits.
+//   A tile takes its time however few there are, and the streaming kernel's
+//   smaller ones, two workgroups per CU, spread the work; half the CUs' worth of
+//   large tiles is about one round of it: 128 tiles, 4 experts of 4096 x 4096 at 75
+//   slots 116 / 127, 8 of 2048 x 2048 80 / 80; 144, 4 of 4096 x 4608 135 / 133, 8 of 2048
+//   x 2304 96 / 82, 16 of 1024 x 1152 68 / 58; 224, 4 of 4096 x 7168 208 / 167, 8 of
+//   4096 x 3584 213 / 160, 32 of 1024 x 896 88 / 63.
+//   From 16 experts on, half the CUs is enough at 65 to 120 slots, where an expert
+//   takes two 64-slot tiles but one of 128 (128 tiles at 75: 16 of 1024 x 1024 60 /
+//   55, 32 of 1024 x 512 64 / 57; at 52 and 16 experts 53 / 56).
+//   With 8 to 15 experts of up to 56 slots, one 64-slot tile each, the streaming
+//   kernel keeps its round (8 of 4096 x 2304 at 52 101 / 114, x 3072 120 / 128; 4 of
+//   4096 x 6144 166 / 140; 8 of 4096 x 2304 at 62 124 / 116).
+//   At 121 to 127, with half-filled 256-slot tiles, 8 experts take three quarters
+//   of the CUs (144 tiles, 8 of 2048 x 2304 100 / 106; 192, x 3072 127 / 116) and
+//   fewer a tile for every CU (4 of 1024 x 7168 120 / 129).
+inline bool few_experts_tiled(int ne, size_t expect, size_t blocks) {
+  if (blocks >= kCUs) return true;
+  const bool more = 2 * blocks > kCUs;
+  if (expect > static_cast<size_t>(kTileNarrow)) return ne >= 16 ? more : ne >= 8 && 4 * blocks >= 3 * kCUs;
+  if (ne >= 16 && 2 * blocks == kCUs) return expect > 64;
+  return more && (expect > 56 || ne < 8 || ne >= 16);
+}
+
 // Which GEMM kernels serve a range, from its expected slots per expert
 // S / ne: up to 48, the decode kernels (weights streamed in registers, exact
 // code-domain arithmetic, up to four 16-slot tiles per pass); above, the
@@ -56,15 +82,8 @@ constexpr int kOneTileBelow = 128;
 // (64-slot tiles). The streaming kernel serves
 //   bit-plane layers, and shapes whose down projection is not a multiple of
 //   256 rows;
-//   ranges below 128 slots per expert whose gate/up has fewer tiles than the
-//   chip has CUs: a tile takes its time however few there are, and smaller
-//   tiles spread the work (streaming / tiled, us a step, one tile per expert
-//   and 128 rows of F: 4 experts of 1024 x 2048 at 80 slots 46 / 55, of 4096 x
-//   4096 107 / 122, 8 of 1024 x 2048 54 / 58 and at 126 slots 61 / 76; with the
-//   chip filled, 8 of 2048 x 4096 at 80 129 / 92, 16 of 1024 x 2048 82 / 63, 8 of
-//   4096 x 14336 614 / 480). From 16 experts on half the chip is enough at 65
-//   to 120 slots, where an expert takes two 64-slot tiles but one of 128: 16
-//   of 2048 x 1024 at 80 81 / 74, 32 of 1024 x 512 62 / 55;
+//   ranges below 128 slots per expert whose gate/up has tiles for about half of
+//   the CUs or fewer (few_experts_tiled);
 //   shared experts whose tiles do not fill the chip (a few experts with a few
 //   hundred slots each in a decode-sized batch).
 // The last two kernels need 32/64-row staging inside one page, 128-row down
@@ -79,8 +98,7 @@ inline GemmPath pick_path(const pw_layer_desc& d, size_t S, size_t S_all, int ne
   if (expect > 48 && tiles && d.H % 256 == 0) {
     const size_t blocks = static_cast<size_t>(ne) * (d.F / 128);
     if (shared) return blocks * ((expect + 255) / 256) < kCUs ? GemmPath::kStream : GemmPath::kTiled;
-    const bool half = ne >= 16 && 2 * blocks >= kCUs && expect > 64 && expect <= kTileNarrow;
-    return expect >= kOneTileBelow || blocks >= kCUs || half ? GemmPath::kTiled : GemmPath::kStream;
+    return expect >= kOneTileBelow || few_experts_tiled(ne, expect, blocks) ? GemmPath::kTiled : GemmPath::kStream;
   }
   if (expect > 48 && tiles && d.H % 128 == 0) return GemmPath::kStream;
   return GemmPath::kDecode;

@@ -39,12 +39,16 @@ class Plan:
 
 
 @pytest.mark.parametrize("E,K,H,F,slots,path", [
-    # gate/up tiles below the 256 CUs: the streaming kernel up to 127 slots ...
+    # gate/up tiles for at most half of the 256 CUs: the streaming kernel up to 127 slots ...
     (4, 1, 512, 512, 50, STREAM), (4, 1, 1024, 2048, 126, STREAM), (4, 2, 4096, 4096, 80, STREAM),
     (8, 2, 256, 512, 75, STREAM), (8, 2, 1024, 2048, 100, STREAM), (16, 2, 1024, 1024, 50, STREAM),
     (16, 2, 1024, 1024, 124, STREAM), (8, 2, 1024, 2048, 128, TILED), (4, 1, 512, 512, 128, TILED),
-    # ... but for 16 or more experts of 65 to 120 slots, and half the CUs
+    # ... but for 16 or more experts of 65 to 120 slots and half the CUs ...
     (16, 2, 1024, 1024, 65, TILED), (32, 4, 1024, 512, 120, TILED), (32, 4, 1024, 384, 80, STREAM),
+    # ... more than half the CUs, but 8 to 15 experts up to 56 slots or above 120
+    (4, 2, 4096, 4608, 52, TILED), (8, 2, 4096, 2304, 56, STREAM), (8, 2, 4096, 2304, 57, TILED),
+    (16, 2, 1024, 1152, 52, TILED), (8, 2, 3072, 3712, 75, TILED), (4, 2, 4096, 7168, 124, STREAM),
+    (8, 2, 2048, 2304, 124, STREAM), (8, 2, 2048, 3072, 124, TILED), (16, 2, 1024, 1152, 124, TILED),
     # a tile for every CU
     (8, 2, 2048, 4096, 50, TILED), (8, 2, 4096, 14336, 75, TILED), (64, 6, 1024, 512, 124, TILED),
     # no 256-row down blocks
